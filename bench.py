@@ -44,7 +44,35 @@ KERNEL_SOURCES = {
     # the digit GEMM, its persistent form and their folds (the digitize passes
     # live in int8_digitize_kernel.h)
     2: ["int8_digits_kernel.h", "int8_digits_persistent.h", "int8_fold.h"],
+    # an AUTO call's INT8 product in the residue form
+    3: ["rns_kernel.h"],
 }
+
+# the residue form's moduli, in the order it takes them
+RESIDUE_MODULI = (256, 255, 253, 251, 247, 241, 239, 233, 229, 227, 223, 217, 211, 199, 197, 193, 191, 181, 179, 173)
+
+
+def residue_moduli(p, k):
+    """Moduli of the residue form for a product of inner dimension k mod p."""
+    need, total = math.log2(k) + 2 * math.log2(p // 2) + 1.05, 0.0
+    for n, m in enumerate(RESIDUE_MODULI, 1):
+        total += math.log2(m)
+        if total >= need:
+            return n
+    return 0
+
+
+def int8_kernel(plan, phases, p, k):
+    """(kernel, phase, INT8 products per k-term and output, planes' bytes per
+    entry, description) of the INT8 product that ran."""
+    if "rns_gemm" in phases:
+        n = residue_moduli(p, k)
+        return "rns_gemm_kernel", "rns_gemm", n, n, f"residues mod {n} one-byte moduli on INT8 MFMA"
+    d = plan["digits_a"]
+    desc = f"{d} signed 8-bit digits per entry on INT8 MFMA"
+    if "int8_gemm_persistent" in phases:  # many short tiles: the persistent form of the digit GEMM
+        return "int8_digits_gemm_persistent_kernel", "int8_gemm_persistent", d * d, d, desc
+    return "int8_digits_gemm_kernel", "int8_gemm", d * d, d, desc
 
 
 def source_digest(form):
@@ -71,19 +99,21 @@ def traffic_for(workload, kernel, digest):
     return rec.get("hbm_bytes_per_launch")
 
 
-def binding_roof(plan, m, n, k, work, peak, unit, kern_ms):
+def binding_roof(plan, m, n, k, work, peak, unit, kern_ms, planes=0):
     """The roof that binds the dominant kernel, and its fraction.
 
     Algorithmic HBM bytes: the binary64 operands read once and C written
     once (FP64 words), or both operands' digit planes read once and C
-    written once (INT8 digits).  The roof that binds is the one whose time
+    written once (INT8 digits), or `planes` residue bytes an entry of all
+    three (the residue form's product kernel).  The roof that binds is the one whose time
     at peak is the larger: the MFMA work (`work` at `peak` in `unit`) or
     those bytes at 8 TB/s."""
     mn, mk, kn = float(m) * n, float(m) * k, float(k) * n
     if plan["form"] == 1:
         alg_bytes = 8.0 * (mk + kn + mn)
     else:
-        alg_bytes = plan["digits_a"] * mk + plan["digits_b"] * kn + 8.0 * mn
+        a, b, c = (planes, planes, planes) if planes else (plan["digits_a"], plan["digits_b"], 8.0)
+        alg_bytes = a * mk + b * kn + c * mn
     if alg_bytes / (HBM_PEAK_GBS * 1e9) > work / (peak * 1e12):
         achieved = alg_bytes / (kern_ms * 1e-3) / 1e9 if kern_ms > 0 else 0.0
         bound, peak, unit = "hbm", HBM_PEAK_GBS, "GB/s"
@@ -463,10 +493,10 @@ def _leg(mmp, torch, dA, dB, p, u, v, steps, ref=None, **kw):
                 "kblock": pl["kblock"], "slots": pl["slots"], "biased_reduction": bool(pl["biased"]),
                 "extended_block": bool(pl["extended"]), "centered_words": bool(pl["centered"])}
     else:
-        phase = "int8_gemm_persistent" if "int8_gemm_persistent" in phases else "int8_gemm"
-        peak, work = INT8_MFMA_PEAK_TOPS, 2.0 * pl["digits_a"] * pl["digits_b"] * mnk
-        desc = {"form": "int8_digits", "dtype": "int8 digits, int32 accumulation, f64 fold",
-                "digits": pl["digits_a"]}
+        _, phase, products, _, what = int8_kernel(pl, phases, p, k)
+        peak, work = INT8_MFMA_PEAK_TOPS, 2.0 * products * mnk
+        desc = {"form": "int8_residues" if phase == "rns_gemm" else "int8_digits",
+                "dtype": "int8 words, int32 accumulation, f64 recombination", "words": what}
     launches, tot = phases.get(phase, (0, 0.0))
     kms = tot / max(launches, 1)
     rec = dict(desc)
@@ -704,6 +734,7 @@ def main():
     eff = 2.0 * mnk / (ms * 1e-3) / 1e9
     digest = source_digest(plan["form"])
     workload = prob.tag
+    planes = 0  # residue planes, when that form ran
     if plan["form"] == 1:
         kernel, phase, peak, unit = "fp64_words_kernel", "fp64_words", FP64_MFMA_PEAK_TFLOPS, "TFLOP/s"
         work = 2.0 * plan["u"] * plan["v"] * mnk  # word flops per launch
@@ -713,15 +744,17 @@ def main():
                      + (" (extended bound)" if plan["extended"] else
                         " (centered words)" if plan["centered"] else " (the paper's lambda)"))
     else:
-        kernel, phase, peak, unit = "int8_digits_gemm_kernel", "int8_gemm", INT8_MFMA_PEAK_TOPS, "TOP/s"
-        if "int8_gemm_persistent" in phases:  # many short tiles: the persistent form of the digit GEMM
-            kernel, phase = "int8_digits_gemm_persistent_kernel", "int8_gemm_persistent"
-        work = 2.0 * plan["digits_a"] * plan["digits_b"] * mnk  # digit-product int8 ops per launch
-        dtype = "int8 digits, int32 accumulation, f64 fold"
-        form_desc = f"{plan['digits_a']} signed 8-bit digits per entry on INT8 MFMA"
+        kernel, phase, products, planes, form_desc = int8_kernel(plan, phases, prob.p, prob.k)
+        peak, unit = INT8_MFMA_PEAK_TOPS, "TOP/s"
+        work = 2.0 * products * mnk  # int8 operations per launch
+        dtype = "int8 words, int32 accumulation, f64 recombination"
+        if phase == "rns_gemm":
+            digest = source_digest(3)
+        else:
+            planes = 0
     launches, total_ms = phases.get(phase, (0, 0.0))
     kern_ms = total_ms / max(launches, 1)
-    roofline = binding_roof(plan, prob.m, prob.n, prob.k, work, peak, unit, kern_ms)
+    roofline = binding_roof(plan, prob.m, prob.n, prob.k, work, peak, unit, kern_ms, planes)
     roofline.update({"traffic": traffic_for(workload, kernel, digest), "kernel": kernel,
                      "kernel_ms": round(kern_ms, 4)})
     shape = "square" if prob.m == prob.n == prob.k else "product"
@@ -748,7 +781,8 @@ def main():
             "slots": plan["slots"], "biased_reduction": bool(plan["biased"]),
             "digits": plan["digits_a"], "extended_block": bool(plan["extended"]),
             "centered_words": bool(plan["centered"]),
-            "form": "fp64_words" if plan["form"] == 1 else "int8_digits", "tile": plan["tile"],
+            "form": "fp64_words" if plan["form"] == 1 else "int8_residues" if planes else "int8_digits",
+            "tile": plan["tile"],
         },
         "roofline": roofline,
         "phases_ms_per_step": {k: round(v[1] / max(args.steps, 1), 4) for k, v in phases.items()},

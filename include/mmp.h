@@ -61,7 +61,13 @@ typedef enum {
 
 /* Word forms. */
 enum {
-  MMP_FORM_AUTO = 0,        /* planner picks the faster form for (p, shape) */
+  MMP_FORM_AUTO = 0,        /* planner picks the faster form for (p, shape); a
+                               single product planned on INT8 words then runs
+                               on its signed digits, or, where that is the
+                               faster way to the same result, on its residues
+                               modulo pairwise coprime moduli of one INT8 word
+                               each (one INT8 product per modulus, recombined
+                               by the Chinese remainder theorem mod p) */
   MMP_FORM_FP64_WORDS = 1,  /* the paper's binary64 words on FP64 MFMA */
   MMP_FORM_INT8_WORDS = 2   /* signed 8-bit digits on INT8 MFMA, int32
                                accumulation, binary64 reduction/recombination */
@@ -169,7 +175,11 @@ typedef struct {
   double q;               /* fl(1/p) */
   double est_seconds;     /* planner's cost-model estimate (0 if unknown) */
   int splits;             /* split-K k-ranges (1: none) */
-  size_t workspace_bytes; /* device workspace the call needs */
+  size_t workspace_bytes; /* device workspace the call needs (an AUTO call
+                             on INT8 words: what its digits need; given a
+                             caller's workspace too small for the residues'
+                             planes, up to 20 bytes per entry of A, B and C,
+                             it runs on the digits) */
   int centered;           /* 1: centered words and the round-to-nearest
                              in-loop reduction (mmp_opts.centered_words) */
   int biased;             /* 1: the correction-free in-loop reduction is the

@@ -220,12 +220,69 @@ Int8Args make_int8_args(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t k, c
   return g;
 }
 
+int run_planned(const mmp_plan_t& pl, const mmp_opts* opts, int64_t m, int64_t n, int64_t k, const double* A,
+                int64_t lda, const double* B, int64_t ldb, double* C, int64_t ldc, void* stream) {
+  const mmp_operand_t* pa = opts ? opts->prepared_a : nullptr;
+  const mmp_operand_t* pb = opts ? opts->prepared_b : nullptr;
+  if (m == 0 || n == 0) return MMP_OK;
+  if (k == 0) return hip_status(launch_zero_fill(C, m, n, ldc, stream));
+  if (opts && opts->validate_entries)
+    if (int st = validate_product_entries(pl.p, m, n, k, A, lda, B, ldb, stream)) return st;
+
+  // the residue form of an INT8 product where it is the faster one
+  RnsPlan rp;
+  if (pl.form == MMP_FORM_INT8_WORDS && rns_chosen(pl.p, m, n, k, opts, &rp)) {
+    void* work = nullptr;
+    bool owned = false;
+    // a caller's workspace sized for the digit planes (or not on the 16 bytes
+    // that the planes' words take), or no memory for the residue planes: the
+    // digit form
+    const bool fits = !opts || ((uintptr_t)opts->workspace % 16) == 0;
+    const int st = fits ? acquire_workspace(rp.bytes, opts, stream, &work, &owned) : MMP_EINVAL;
+    if (st != MMP_OK && !(opts && opts->workspace)) (void)hipGetLastError();  // the launches below report their own
+    if (st == MMP_OK) {
+      const Int8Args g = make_int8_args(pl, m, n, k, A, lda, B, ldb, C, ldc, (int8_t*)work);
+      const int st1 = hip_status(launch_rns(rp, g, stream));
+      const int st2 = release_workspace(work, owned, stream);
+      return st1 ? st1 : st2;
+    }
+  }
+  // split-K residues go after the digit planes made per call (INT8) or
+  // fill the workspace (FP64)
+  const size_t planes = pl.form == MMP_FORM_INT8_WORDS
+                            ? int8_planes_bytes(pl.digits_a, m, n, k, pa != nullptr, pb != nullptr) : 0;
+  const size_t need = planes + (pl.splits > 1 ? 8 * (size_t)pl.splits * (size_t)m * (size_t)n : 0);
+  void* work = nullptr;
+  bool owned = false;
+  if (int st = acquire_workspace(need, opts, stream, &work, &owned)) return st;
+  double* partial = pl.splits > 1 ? (double*)((char*)work + planes) : nullptr;
+  int e;
+  if (pl.form == MMP_FORM_INT8_WORDS) {
+    Int8Args g = make_int8_args(pl, m, n, k, A, lda, B, ldb, C, ldc, (int8_t*)work);
+    g.resident_a = pa ? pa->planes : nullptr;
+    g.resident_b = pb ? pb->planes : nullptr;
+    g.splits = pl.splits;
+    g.partial = partial;
+    e = launch_int8_digitize(pl.digits_a, g, stream);
+    if (!e) e = launch_int8_gemm(pl.digits_a, &g, 1, stream);
+  } else {
+    Fp64Batch b;
+    std::memset(&b, 0, sizeof(b));
+    b.njobs = 1;
+    b.job[0] = make_fp64_args(pl, m, n, k, A, lda, B, ldb, C, ldc);
+    b.job[0].splits = pl.splits;
+    b.job[0].partial = partial;
+    e = launch_fp64_words(pl.u, pl.v, pl.tile, b, stream);
+  }
+  if (!e && pl.splits > 1) e = launch_splitk_reduce(partial, pl.splits, m, n, (double)pl.p, C, ldc, stream);
+  const int st = hip_status(e);
+  const int st2 = release_workspace(work, owned, stream);
+  return st ? st : st2;
+}
+
 }  // namespace mmp
 
-namespace {
 using namespace mmp;
-
-}  // namespace
 
 extern "C" {
 
@@ -340,42 +397,7 @@ int mm_modp_async(const mmp_opts* opts, uint64_t p, int u, int v, int64_t m, int
       o2.form = MMP_FORM_INT8_WORDS;
       if (int st = mmp::plan(p, 0, 0, m, n, k, &o2, &pl)) return st;
     }
-    if (m == 0 || n == 0) return MMP_OK;
-    if (k == 0) return hip_status(launch_zero_fill(C, m, n, ldc, stream));
-    if (opts && opts->validate_entries)
-      if (int st = validate_product_entries(p, m, n, k, A, lda, B, ldb, stream)) return st;
-
-    // split-K residues go after the digit planes made per call (INT8) or
-    // fill the workspace (FP64)
-    const size_t planes = pl.form == MMP_FORM_INT8_WORDS
-                              ? int8_planes_bytes(pl.digits_a, m, n, k, pa != nullptr, pb != nullptr) : 0;
-    const size_t need = planes + (pl.splits > 1 ? 8 * (size_t)pl.splits * (size_t)m * (size_t)n : 0);
-    void* work = nullptr;
-    bool owned = false;
-    if (int st = acquire_workspace(need, opts, stream, &work, &owned)) return st;
-    double* partial = pl.splits > 1 ? (double*)((char*)work + planes) : nullptr;
-    int e;
-    if (pl.form == MMP_FORM_INT8_WORDS) {
-      Int8Args g = make_int8_args(pl, m, n, k, A, lda, B, ldb, C, ldc, (int8_t*)work);
-      g.resident_a = pa ? pa->planes : nullptr;
-      g.resident_b = pb ? pb->planes : nullptr;
-      g.splits = pl.splits;
-      g.partial = partial;
-      e = launch_int8_digitize(pl.digits_a, g, stream);
-      if (!e) e = launch_int8_gemm(pl.digits_a, &g, 1, stream);
-    } else {
-      Fp64Batch b;
-      std::memset(&b, 0, sizeof(b));
-      b.njobs = 1;
-      b.job[0] = make_fp64_args(pl, m, n, k, A, lda, B, ldb, C, ldc);
-      b.job[0].splits = pl.splits;
-      b.job[0].partial = partial;
-      e = launch_fp64_words(pl.u, pl.v, pl.tile, b, stream);
-    }
-    if (!e && pl.splits > 1) e = launch_splitk_reduce(partial, pl.splits, m, n, (double)p, C, ldc, stream);
-    const int st = hip_status(e);
-    const int st2 = release_workspace(work, owned, stream);
-    return st ? st : st2;
+    return run_planned(pl, opts, m, n, k, A, lda, B, ldb, C, ldc, stream);
   } catch (...) {
     return MMP_EINVAL;
   }

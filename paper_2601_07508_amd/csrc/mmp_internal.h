@@ -192,6 +192,22 @@ int launch_int8_gemm(int digits, const Int8Args* jobs, int njobs, void* stream);
 constexpr int kMaxMixedBatch = 64;
 int launch_int8_batch(const Int8Args* jobs, const int* digits, int njobs, void* stream);
 
+// Residue form of an INT8 product (rns_kernel.h): n moduli of at most 256,
+// `splits` k-ranges, and a workspace of A's planes, B's planes and the
+// outputs' residue bytes.
+constexpr int kRnsMaxModuli = 20;
+struct RnsPlan {
+  int n, splits;
+  bool large;  // 256 x 256 tiles, else 128 x 128
+  size_t bytes_a, bytes_b, bytes;
+  double us;   // estimated time
+};
+int rns_moduli(double log2_bound);  // moduli for integers up to 2^log2_bound in magnitude (0: too many)
+// True (and *r) when an AUTO call's INT8 product of these sizes and options is
+// estimated faster in the residue form than on its digit planes.
+bool rns_chosen(uint64_t p, int64_t m, int64_t n, int64_t k, const mmp_opts* opts, RnsPlan* r);
+int launch_rns(const RnsPlan& r, const Int8Args& g, void* stream);
+
 // Phase timer hooks (null tokens unless mmp_timers_enable(1)).  A launch
 // passes timer_start(t) / timer_stop(t) as the start and stop events of
 // hipExtLaunchKernelGGL, then hands the token back with timer_commit.
@@ -252,6 +268,12 @@ Fp64Args make_fp64_args(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t k, c
                         const double* B, int64_t ldb, double* C, int64_t ldc);
 Int8Args make_int8_args(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
                         const double* B, int64_t ldb, double* C, int64_t ldc, int8_t* work);
+
+// One product as planned (arguments checked): entry validation if asked for,
+// workspace, launches.  An INT8 plan of an AUTO call takes the residue form
+// where rns_chosen says so.
+int run_planned(const mmp_plan_t& pl, const mmp_opts* opts, int64_t m, int64_t n, int64_t k, const double* A,
+                int64_t lda, const double* B, int64_t ldb, double* C, int64_t ldc, void* stream);
 
 // Scan for entries outside [0, p) or non-integral; sets *flag (device int) nonzero.
 int launch_validate(const double* X, int64_t rows, int64_t cols, int64_t ld, double p, int* flag,

@@ -1,0 +1,295 @@
+// Residue form of the INT8 product (rns_kernel.h): moduli, constants, the
+// choice of tile and k-ranges, and the three launches.
+#include <algorithm>
+#include <atomic>
+#include <cmath>
+#include <cstring>
+#include <type_traits>
+
+#include "rns_kernel.h"
+
+namespace mmp {
+
+namespace {
+
+// The largest pairwise coprime integers up to 256, greedily.
+const int kModuli[kRnsMaxModuli] = {256, 255, 253, 251, 247, 241, 239, 233, 229, 227,
+                                    223, 217, 211, 199, 197, 193, 191, 181, 179, 173};
+
+int inv_mod_small(int x, int m) {
+  x %= m;
+  for (int i = 1; i < m; i++)
+    if ((int64_t)x * i % m == 1) return i;
+  return 0;
+}
+
+uint32_t float_bits(float f) {
+  uint32_t u;
+  std::memcpy(&u, &f, 4);
+  return u;
+}
+
+// O = the first multiple of 256 m at or above `from`, as a binary32 pattern,
+// and the constants that reduce O + y (rns_kernel.h, ConvConst).
+void reduction(int m, int64_t from, uint32_t* bits, float* inv, float* magic) {
+  const int64_t step = 256 * (int64_t)m, O = (from + step - 1) / step * step;
+  *bits = float_bits((float)O);
+  *inv = 1.0f / (float)m;
+  *magic = (float)(12582912 - O / m);
+}
+
+// Everything that depends on the moduli alone, made once.
+struct Tables {
+  rns::ConvConst conv[kRnsMaxModuli];
+  rns::GemmConst gemm[kRnsMaxModuli];
+  int inv[kRnsMaxModuli + 1][kRnsMaxModuli];  // [n][t]: (M / m_t)^-1 mod m_t for M = m_0 .. m_(n-1), within m_t / 2
+  double log2M[kRnsMaxModuli + 1];
+  Tables() {
+    log2M[0] = 0.0;
+    for (int t = 0; t < kRnsMaxModuli; t++) {
+      const int m = kModuli[t];
+      log2M[t + 1] = log2M[t] + std::log2((double)m);
+      rns::ConvConst& c = conv[t];
+      uint32_t w[2] = {0, 0};
+      int64_t pw = 1;
+      for (int i = 0; i < 8; i++) {
+        int s = (int)(pw % m);
+        if (s > 127) s -= m;
+        w[i / 4] |= (uint32_t)(uint8_t)s << (8 * (i % 4));
+        pw = pw * 256 % m;
+      }
+      c.wlo = (int32_t)w[0];
+      c.whi = (int32_t)w[1];
+      c.negm = -m;
+      reduction(m, (1 << 23) + (1 << 17), &c.bits, &c.inv, &c.magic);
+      rns::GemmConst& g = gemm[t];
+      g.mul = (uint32_t)(65536 % m) << 16 | 1u;
+      g.negm = -m;
+      g.bias = (1 << 30) / m * m;
+      reduction(m, 1 << 23, &g.bits, &g.inv, &g.magic);
+    }
+    for (int n = 0; n <= kRnsMaxModuli; n++)
+      for (int t = 0; t < n; t++) {
+        const int m = kModuli[t];
+        int x = 1;
+        for (int j = 0; j < n; j++)
+          if (j != t) x = x * (kModuli[j] % m) % m;
+        const int i = inv_mod_small(x, m);
+        inv[n][t] = 2 * i > m ? i - m : i;
+      }
+  }
+};
+const Tables& tables() {
+  static const Tables t;
+  return t;
+}
+
+uint64_t mulmod_u64(uint64_t x, uint64_t y, uint64_t p) { return (uint64_t)((unsigned __int128)x * y % p); }
+
+void split26(uint64_t w, uint64_t p, double* hi, double* lo) {
+  // the representative within p / 2 of zero, as hi 2^26 + lo, 0 <= lo < 2^26
+  const int64_t s = w > p / 2 ? (int64_t)w - (int64_t)p : (int64_t)w;
+  const int64_t h = s >> 26;
+  *hi = (double)h;
+  *lo = (double)(s - h * (1 << 26));
+}
+
+int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+int current_cus() {
+  static std::atomic<int> cache[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0) dev = 0;
+  if (dev < 64 && cache[dev].load(std::memory_order_relaxed) > 0) return cache[dev].load(std::memory_order_relaxed);
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
+  if (dev < 64) cache[dev].store(cus, std::memory_order_relaxed);
+  return cus;
+}
+
+template <class S>
+int launch_products(const RnsPlan& r, const Int8Args& g, int8_t* planes, hipStream_t s) {
+  using namespace rns;
+  RnsGemmArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.Ad = planes;
+  a.Bd = planes + r.bytes_a;
+  a.res = planes + r.bytes_a + r.bytes_b;
+  a.kp = g.kp;
+  a.ablk = (int)row_blocks(g.m);
+  a.bblk = (int)row_blocks(g.n);
+  a.tiles_m = (int)cdiv(g.m, S::BM);
+  a.tiles_n = (int)cdiv(g.n, S::BN);
+  a.n = r.n;
+  a.splits = r.splits;
+  a.stages = (int)(g.kp / 64);
+  a.per_split = (int)cdiv(a.stages, r.splits);
+  std::memcpy(a.c, tables().gemm, sizeof(a.c));
+  const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n, items = tiles * r.n * r.splits;
+  const int64_t grid = std::min<int64_t>(items, (int64_t)current_cus() * S::GROUPS);
+  TimerTok* t = timer_begin("rns_gemm");
+  hipExtLaunchKernelGGL((rns_gemm_kernel<S>), dim3((unsigned)grid), dim3(S::THREADS), 0, s, timer_start(t),
+                        timer_stop(t), 0, a);
+  int e = (int)hipGetLastError();
+  timer_commit(t, e);
+  if (e) return e;
+
+  CombineArgs b;
+  std::memset(&b, 0, sizeof(b));
+  b.res = a.res;
+  b.C = g.C;
+  b.m = g.m;
+  b.n = g.n;
+  b.ldc = g.ldc;
+  b.tiles_m = a.tiles_m;
+  b.tiles_n = a.tiles_n;
+  b.nmod = r.n;
+  b.splits = r.splits;
+  b.p = (double)g.p;
+  b.q = g.q;
+  // M / m_t mod p as the product of the moduli before t and those after it
+  uint64_t after[kRnsMaxModuli + 1], before = 1;
+  after[r.n] = 1;
+  for (int i = r.n - 1; i >= 0; i--) after[i] = mulmod_u64(after[i + 1], (uint64_t)kModuli[i], g.p);
+  split26(after[0] % g.p, g.p, &b.mhi, &b.mlo);
+  for (int i = 0; i < r.n; i++) {
+    const int inv = tables().inv[r.n][i];
+    const uint64_t iv = (uint64_t)(inv < 0 ? inv + (int64_t)g.p : inv);  // p >= 2^16
+    split26(mulmod_u64(mulmod_u64(before, after[i + 1], g.p), iv, g.p), g.p, &b.whi[i], &b.wlo[i]);
+    b.f[i] = (double)inv / (double)kModuli[i];
+    before = mulmod_u64(before, (uint64_t)kModuli[i], g.p);
+  }
+  const int64_t units = tiles * S::NW * S::XB * S::YB / 4;
+  t = timer_begin("rns_combine");
+  hipExtLaunchKernelGGL((rns_combine_kernel<S>), dim3((unsigned)cdiv(units, 4)), dim3(256), 0, s, timer_start(t),
+                        timer_stop(t), 0, b);
+  e = (int)hipGetLastError();
+  timer_commit(t, e);
+  return e;
+}
+
+}  // namespace
+
+// Moduli whose product exceeds 2^1.05 bound (|X| <= bound), 0 if none: log2 M
+// and log2 bound are binary64 sums of at most 21 logarithms, good to 1e-12.
+int rns_moduli(double log2_bound) {
+  for (int n = 1; n <= kRnsMaxModuli; n++)
+    if (tables().log2M[n] >= log2_bound + 1.05) return n;
+  return 0;
+}
+
+namespace {
+
+// Estimates in microseconds, fitted (least relative squares) to 260 products
+// with m, n, k log-uniform up to 12000 (k to 131072) and 18 to 52 bits, each
+// timed in both forms on one MI355X: within 10% of the measured time for 80%
+// of the products in the residue form and 18% in the digit form.  Choosing by
+// them costs 0.8% over always choosing right.
+//
+// Digit form: a fixed part, the planes (8 bytes read and D written an entry),
+// the digit products (by work, by rounds of workgroups and by the length of
+// one workgroup's chain) and the outputs.
+double digits_us(int64_t m, int64_t n, int64_t k, int D) {
+  const int64_t st = cdiv(k, 64);
+  const int s = choose_splits_fill(cdiv(m, 64) * cdiv(n, 64), st, 32);
+  const int64_t items = cdiv(m, 64) * cdiv(n, n <= 32 ? 32 : 64) * s;
+  const double chain = (double)cdiv(st, s), stage = (double)D * D * (n <= 32 ? 0.5 : 1.0);
+  return 12.7 + 0.233e-6 * ((double)m + n) * k * (8 + D) + 0.0558 * (double)items * chain * stage / 512 +
+         0.0162 * (double)cdiv(items, D <= 5 ? 512 : 256) * chain * stage + 0.0119 * chain * D * D + 0.22 * chain +
+         2.4e-6 * (double)m * n * (s > 1 ? s + 1 : 1);
+}
+
+// Residue form: a fixed part, the planes (N written an entry, and read by the
+// products), the products by rounds of workgroups, and the residue bytes
+// (written, then read) with the outputs.
+double residues_us(const RnsPlan& r, int64_t m, int64_t n, int64_t k, int64_t items, int64_t per) {
+  const double entries = ((double)m + n) * k, rows = entries * r.n;
+  const double out = 0.22e-6 * (double)m * n * (2.0 * r.n * r.splits + 8);
+  if (r.large)
+    return 15.1 + 0.233e-6 * entries * (8 + r.n) + 0.0575e-6 * rows + 0.65 * (double)(cdiv(items, 256) * per) + out +
+           r.n * (0.11 + 0.256 * r.splits);
+  return 14.0 + 0.209e-6 * entries * (8 + r.n) + 0.153e-6 * rows + 0.339 * (double)(cdiv(items, 512) * per) + out +
+         r.n * (0.064 + 0.246 * r.splits);
+}
+
+// One tile shape's plan for nm moduli; false beyond the kernels' index ranges.
+template <class S>
+bool plan_shape(int nm, int64_t m, int64_t n, int64_t k, RnsPlan* r) {
+  using namespace rns;
+  const int64_t stages = cdiv(k, 64), kp = stages * 64, tiles = cdiv(m, S::BM) * cdiv(n, S::BN);
+  const int64_t slots = 256 * S::GROUPS;
+  // k-ranges: at most 1024 stages each (the int32 bound), and while the items
+  // do not fill the chip more, of at least 16 stages
+  int64_t s = cdiv(stages, 1024);
+  while (tiles * nm * s < slots && stages / (s + 1) >= 16 && s < 64) s++;
+  if (s > 64) return false;
+  const int64_t per = cdiv(stages, s);
+  r->n = nm;
+  r->splits = (int)cdiv(stages, per);  // no empty range
+  r->large = std::is_same<S, RnsLarge>::value;
+  const int64_t items = tiles * nm * r->splits;
+  const int64_t parts = row_blocks(m) * cdiv(kp, 256) + cdiv(n, 64) * stages;  // conversion workgroups
+  if (items > 0x3fffffff || tiles * 64 > 0x7fffffff || parts > 0x7fffffff) return false;
+  // copies address an operand's plane with 32-bit offsets
+  if (row_blocks(std::max(m, n)) * 16 * kp >= ((int64_t)1 << 32)) return false;
+  r->bytes_a = (size_t)nm * row_blocks(m) * 16 * kp;
+  r->bytes_b = (size_t)nm * row_blocks(n) * 16 * kp;
+  r->bytes = r->bytes_a + r->bytes_b + (size_t)items * S::TILE_BYTES;
+  r->us = residues_us(*r, m, n, k, items, per);
+  return true;
+}
+
+}  // namespace
+
+// Device memory a product may take in this form; beyond it the digit form's
+// planes, two to three times smaller, are used.
+constexpr size_t kRnsMaxBytes = (size_t)16 << 30;
+
+bool rns_chosen(uint64_t p, int64_t m, int64_t n, int64_t k, const mmp_opts* opts, RnsPlan* r) {
+  using namespace rns;
+  // what asks for the digit form: MMP_FORM_INT8_WORDS by name, prepared planes, a
+  // forced block or k-ranges.  From three digits on (one or two digits need at
+  // most four products, and the recombination's bounds take p >= 2^16).
+  if (opts && (opts->form != MMP_FORM_AUTO || opts->prepared_a || opts->prepared_b || opts->force_kblock ||
+               opts->splits))
+    return false;
+  if (m <= 0 || n <= 0 || k <= 0 || p < (1u << 16)) return false;
+  if (std::max(std::max(m, n), k) > 0x7fffffff) return false;
+  const int nm = rns_moduli(std::log2((double)k) + 2.0 * std::log2((double)(p / 2)));
+  if (nm == 0) return false;
+  RnsPlan small;
+  if (!plan_shape<RnsSmall>(nm, m, n, k, &small)) return false;
+  *r = small;
+  RnsPlan large;
+  if (plan_shape<RnsLarge>(nm, m, n, k, &large) && large.us < small.us) *r = large;
+  if (r->bytes > kRnsMaxBytes) return false;
+  return r->us < digits_us(m, n, k, digits_for(p));
+}
+
+int launch_rns(const RnsPlan& r, const Int8Args& g, void* stream) {
+  using namespace rns;
+  hipStream_t s = (hipStream_t)stream;
+  int8_t* planes = g.work;
+  ConvArgs ca;
+  ca.n = r.n;
+  std::memcpy(ca.c, tables().conv, sizeof(ca.c));
+  const CenteredIn A{g.A, (int64_t)g.p, (int64_t)(g.p / 2)}, B{g.B, (int64_t)g.p, (int64_t)(g.p / 2)};
+  const int64_t na = row_blocks(g.m) * cdiv(g.kp, 256), nb = cdiv(g.n, 64) * (g.kp / 64);
+  // moduli in up to four parts while the grid is under four workgroups a CU
+  unsigned parts = 1;
+  while (parts < 4 && (na + nb) * parts < 1024) parts *= 2;
+  const dim3 grid((unsigned)(na + nb), parts);
+  TimerTok* t = timer_begin("rns_convert");
+  if (g.p >> 31)
+    hipExtLaunchKernelGGL((rns_convert_kernel<CenteredIn, true>), grid, dim3(256), 0, s, timer_start(t), timer_stop(t), 0, ca, A, g.m, g.lda, B, g.n, g.ldb, g.k, g.kp, planes,
+                          planes + r.bytes_a, na);
+  else
+    hipExtLaunchKernelGGL((rns_convert_kernel<CenteredIn, false>), grid, dim3(256), 0, s, timer_start(t), timer_stop(t), 0, ca, A, g.m, g.lda, B, g.n, g.ldb, g.k, g.kp, planes,
+                          planes + r.bytes_a, na);
+  const int e = (int)hipGetLastError();
+  timer_commit(t, e);
+  if (e) return e;
+  return r.large ? launch_products<RnsLarge>(r, g, planes, s) : launch_products<RnsSmall>(r, g, planes, s);
+}
+
+}  // namespace mmp

@@ -75,9 +75,11 @@ int mmp_autotune(uint64_t p, int64_t m, int64_t n, int64_t k, const mmp_opts* op
       o.form = c.form;
       o.tile = c.tile;
       o.force_kblock = c.form == MMP_FORM_FP64_WORDS ? c.kblock : 0;
-      auto once = [&]() {
-        return mm_modp_async(&o, p, c.u, c.v, m, n, k, A, k, B, n, C, n, s);
-      };
+      // an INT8 candidate runs as an AUTO call of that plan would (residue or digit form)
+      mmp_plan_t pl;
+      if (plan(p, c.u, c.v, m, n, k, &o, &pl) != MMP_OK) continue;
+      const mmp_opts& ran = c.form == MMP_FORM_INT8_WORDS ? base : o;
+      auto once = [&]() { return run_planned(pl, &ran, m, n, k, A, k, B, n, C, n, s); };
       int st = once();  // warm-up (also loads the kernel)
       if (st != MMP_OK) continue;
       // repeat so that a measurement spans at least a few milliseconds

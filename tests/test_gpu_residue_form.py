@@ -1,0 +1,148 @@
+"""GPU parity of the INT8 product's residue form against the exact oracle
+(tolerance 0), at the edges of its tiles, k-ranges and int32 range.
+
+Products large enough for the planner to take the form; the launch phases say
+that it ran.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+import mmp_inputs as gen
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+mmp = pytest.importorskip("paper_2601_07508_amd")
+
+P52, P31, P50 = 4503599627370449, 2147483647, 1125899906842597
+
+
+def say(*a):
+    print(*a, file=sys.stderr, flush=True)
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def timed(call):
+    """The launch phases of one call."""
+    mmp.timers_read(reset=True)
+    mmp.timers_enable(True)
+    call()
+    torch.cuda.synchronize()
+    mmp.timers_enable(False)
+    return mmp.timers_read(reset=True)
+
+
+def strided(x, pad, shift):
+    """A device copy of x with leading dimension cols + pad, `shift` entries into its storage."""
+    rows, cols = x.shape
+    flat = torch.full((rows * (cols + pad) + shift + 1,), float("nan"), dtype=torch.float64, device="cuda")
+    view = flat[shift:shift + rows * (cols + pad)].view(rows, cols + pad)[:, :cols]
+    view.copy_(torch.from_numpy(x.astype(np.float64)))
+    return view
+
+
+# tile edges (128 and 256), 16-row blocks, 64-k stages, 4-stage ring, one digit-count
+# boundary and p on both sides of 2^31 (the one- and two-word conversions)
+@pytest.mark.parametrize("p,m,n,k,pad,shift", [
+    (P52, 512, 512, 2048, 0, 0), (P52, 513, 511, 2049, 1, 1), (P50, 257, 640, 3073, 0, 1), (P52, 255, 257, 4159, 3, 0),
+    (P52, 385, 1025, 1985, 2, 0), (P31, 2561, 2545, 4033, 1, 0), (8589934583, 1537, 2050, 2111, 0, 0),
+    (P52, 1040, 2064, 1088, 5, 1),
+])
+def test_edges(p, m, n, k, pad, shift):
+    A = gen.random_matrix(m, 1, m, k, p)
+    B = gen.random_matrix(n, 2, k, n, p)
+    say("residue form", p, m, n, k, pad, shift)
+    dA, dB = strided(A, pad, shift), strided(B, pad, shift)
+    store = torch.full((m + 1, n + pad), -1.0, dtype=torch.float64, device="cuda")
+    phases = timed(lambda: mmp.mm_modp_async(dA, dB, store[:m, :n], p))
+    assert "rns_gemm" in phases, phases
+    got = store.cpu().numpy()
+    want = oracle.mm_modp(p, A, B).astype(np.float64)
+    assert np.array_equal(got[:m, :n], want) and not np.signbit(got[:m, :n]).any()
+    assert (got[m:] == -1.0).all() and (got[:, n:] == -1.0).all()
+
+
+@pytest.mark.parametrize("p,k", [(P52, 65536), (P52, 65600), (P31, 65536)])
+def test_extreme_sums(p, k):
+    # whole k-ranges of 1024 stages with every residue at an end of its range:
+    # x = 128 makes the residue mod 256 -128 in every term; x = (p +- 1) / 2 is
+    # the largest centered entry of either sign
+    m, n = 2048, 2064
+    for x, y in ((128, 128), ((p - 1) // 2, (p - 1) // 2), ((p - 1) // 2, (p + 1) // 2), (p - 128, 128)):
+        say("extreme", p, k, x, y)
+        A = torch.full((m, k), float(x), dtype=torch.float64, device="cuda")
+        B = torch.full((k, n), float(y), dtype=torch.float64, device="cuda")
+        C = torch.empty((m, n), dtype=torch.float64, device="cuda")
+        phases = timed(lambda: mmp.mm_modp_async(A, B, C, p))
+        assert "rns_gemm" in phases, phases
+        assert bool((C == float(x * y * k % p)).all())
+
+
+@pytest.mark.parametrize("n", [512, 770])
+def test_long_k_ranges(n):
+    # few tiles, long k: several k-ranges, the last one shorter
+    p, m, k = P52, 260, 40000
+    A = gen.random_matrix(8, 1, m, k, p)
+    B = gen.random_matrix(9, 2, k, n, p)
+    say("ranges", n)
+    dA, dB = strided(A, 0, 0), strided(B, 0, 0)
+    C = torch.empty((m, n), dtype=torch.float64, device="cuda")
+    phases = timed(lambda: mmp.mm_modp_async(dA, dB, C, p))
+    assert "rns_gemm" in phases, phases
+    assert np.array_equal(C.cpu().numpy(), oracle.mm_modp(p, A, B).astype(np.float64))
+
+
+def test_workspace_of_the_digit_planes_is_enough():
+    # a caller workspace of the plan's size: too small for the residue planes,
+    # so the digit form runs, with the same result
+    p, m, n, k = P52, 512, 520, 2048
+    A = gen.random_matrix(3, 1, m, k, p)
+    B = gen.random_matrix(4, 2, k, n, p)
+    dA, dB = strided(A, 0, 0), strided(B, 0, 0)
+    ws = torch.empty(mmp.plan(p, m, n, k)["workspace_bytes"], dtype=torch.uint8, device="cuda")
+    big = torch.empty(1 << 28, dtype=torch.uint8, device="cuda")
+    want = oracle.mm_modp(p, A, B).astype(np.float64)
+    for w, phase in ((ws, "int8_gemm"), (big, "rns_gemm")):
+        C = torch.full((m, n), -1.0, dtype=torch.float64, device="cuda")
+        phases = timed(lambda: mmp.mm_modp_async(dA, dB, C, p, workspace=w))
+        assert phase in phases, phases
+        assert np.array_equal(C.cpu().numpy(), want)
+    C = torch.full((m, n), -1.0, dtype=torch.float64, device="cuda")
+    phases = timed(lambda: mmp.mm_modp_static(dA, dB, C, p))
+    assert "rns_gemm" in phases and np.array_equal(C.cpu().numpy(), want)
+
+
+def test_captured_in_a_graph():
+    p, m, n, k = P50, 640, 520, 1500
+    dA = strided(gen.random_matrix(5, 1, m, k, p), 0, 0)
+    dB = strided(gen.random_matrix(6, 2, k, n, p), 0, 0)
+    C = torch.empty((m, n), dtype=torch.float64, device="cuda")
+    ws = torch.empty(1 << 28, dtype=torch.uint8, device="cuda")
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    call = lambda: mmp.mm_modp_async(dA, dB, C, p, workspace=ws, stream=s)
+    phases = timed(call)
+    assert "rns_gemm" in phases, phases
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        call()
+    for rep in range(3):
+        A = gen.random_matrix(20 + rep, 1, m, k, p)
+        B = gen.random_matrix(30 + rep, 2, k, n, p)
+        dA.copy_(torch.from_numpy(A.astype(np.float64)))
+        dB.copy_(torch.from_numpy(B.astype(np.float64)))
+        C.fill_(-1.0)
+        ws.zero_()
+        say("replay", rep)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(C.cpu().numpy(), oracle.mm_modp(p, A, B).astype(np.float64))
