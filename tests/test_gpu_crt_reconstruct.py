@@ -163,3 +163,40 @@ def test_crt_job_2048_reconstructed():
         exact = sum(int(A[i, l]) * int(B[l, j]) for l in range(job.k))
         got = sum(int(L[w, i, j]) << (64 * w) for w in range(lf))
         assert got == exact, (i, j)
+
+
+def wide_primes(count):
+    """The largest primes below the entry point's limit on a modulus."""
+    out, x = [], P_MAX + 1
+    while len(out) < count:
+        x = gen.prev_prime(x)
+        out.append(x)
+    return out
+
+
+@pytest.mark.parametrize("moduli", [wide_primes(4), wide_primes(5), gen.crt_primes(count=8), gen.crt_primes(count=9),
+                                    wide_primes(24), gen.crt_primes(count=47), gen.crt_primes(count=48),
+                                    gen.crt_primes(count=49), wide_primes(43), wide_primes(44),
+                                    [2, 3, 5, 7, 11, 13], [2**i + 1 for i in (1, 2, 4, 8, 16, 32)] + wide_primes(1)],
+                         ids=lambda v: f"{len(v)}x{max(v).bit_length()}b")
+def test_contraction_edges(moduli):
+    # both sides of the contraction's range (5 to 48 moduli, constants within
+    # the kernel arguments), its k-steps of eight moduli, the widest moduli, and
+    # integers next to 0 and to the product, where the multiple of M that the
+    # binary64 sum suggests is one too many; 143 entries: a partial last wave
+    assert all(math.gcd(a, b) == 1 for i, a in enumerate(moduli) for b in moduli[i + 1:])
+    M = math.prod(moduli)
+    m, n = 13, 11
+    edge = [0, 1, 2, M - 1, M - 2, M // 2, M // 2 + 1, M // 3, M - M // 2**40, M - M // 2**34, M // 2**40, 2**64 % M]
+    edge = [c % M for c in edge + [M - moduli[0], M - moduli[-1], 1 << 63, (1 << 64) - 1, 255, 256]]
+    raw = gen.uniform_bits(len(moduli), 5, m * n * 56, 62)
+    X = np.empty((m, n), dtype=object)
+    for e in range(m * n):
+        x = 0
+        for c in raw[e * 56:(e + 1) * 56]:
+            x = (x << 62) | int(c)
+        X.flat[e] = edge[e] if e < len(edge) else M - 1 - (x % M) // 2**60 if e % 16 == 0 else x % M
+    say("contraction", len(moduli), M.bit_length())
+    limbs = (M.bit_length() + 63) // 64 + len(moduli) % 3
+    got = to_ints(mmp.crt_reconstruct(residues_of(X, moduli), moduli, limbs=limbs))
+    assert np.array_equal(got, X)
