@@ -337,8 +337,13 @@ def bench_crt(args, mmp, torch, gen):
             log("RESULT OUT OF RANGE", p)
             sys.exit(1)
     mnk = float(job.m) * job.n * job.k
-    d = (job.bits + 1 + 7) // 8
-    gemm_ms = phases.get("crt_gemm", (1, 0.0))[1]
+    # the residue form (one INT8 product per one-byte modulus), or digit products
+    if "rns_gemm" in phases:
+        gemm, bound = "rns_gemm", math.log2(job.k) + 2 * job.bits + 1.05
+        products = next(i for i in range(1, 21) if sum(math.log2(x) for x in RESIDUE_MODULI[:i]) >= bound)
+    else:
+        gemm, products = "crt_gemm", ((job.bits + 1 + 7) // 8) ** 2
+    gemm_ms = phases.get(gemm, (1, 0.0))[1]
     # Chinese remainder reconstruction of the integer product: from all the
     # moduli, and from the shortest prefix whose product exceeds
     # k (2^bits - 1)^2 (eq. CRT2); the two must agree on every entry
@@ -387,8 +392,8 @@ def bench_crt(args, mmp, torch, gen):
         "ms_per_step": round(ms, 4), "primes": len(job.primes), "entry_bits": job.bits,
         "config": {"workload": f"CRT {job.m}x{job.n}x{job.k}, entries < 2^{job.bits}, "
                                f"{len(job.primes)} primes of 31..50 bits"},
-        "roofline": {"bound": "mfma", "kernel": "crt_gemm_kernel", "kernel_ms": round(gemm_ms, 4),
-                     "achieved": round(2 * d * d * mnk / (gemm_ms * 1e-3) / 1e12, 2) if gemm_ms else None,
+        "roofline": {"bound": "mfma", "kernel": gemm + "_kernel", "kernel_ms": round(gemm_ms, 4),
+                     "achieved": round(2 * products * mnk / (gemm_ms * 1e-3) / 1e12, 2) if gemm_ms else None,
                      "peak": INT8_MFMA_PEAK_TOPS, "unit": "TOP/s"},
         "phases_ms": {k: round(v[1], 4) for k, v in phases.items()},
         "reconstruction": rec, "product_counts": counts}), flush=True)

@@ -291,8 +291,11 @@ size_t mmp_workspace_batched(const mmp_job *jobs, int count,
  * paper compares against (Section 5.2): with k within one exact int32 block
  * the integer product's digit-weight sums are formed once on the INT8 matrix
  * cores and every modulus reduces them (one GEMM launch for up to 64
- * moduli); otherwise A and B are reduced mod each p on the device and the
- * products run as a batch.  validate_entries checks the entry bound
+ * moduli); or, where that is faster and for any longer k, the integer product
+ * is formed modulo one-byte moduli (one INT8 product each) and every prime
+ * reduces the integer recombined from them.  Otherwise (a workspace too small
+ * for that, or opts->form set) A and B are reduced mod each p on the device
+ * and the products run one by one.  validate_entries checks the entry bound
  * (MMP_ERANGE).  Capturable into a graph with a caller workspace of
  * mmp_workspace_crt() bytes. */
 int mm_modp_crt(const mmp_opts *opts, const uint64_t *A, int64_t lda,

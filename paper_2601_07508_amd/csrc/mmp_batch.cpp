@@ -159,6 +159,18 @@ bool crt_fast(int64_t k, int entry_bits, int nprimes) {
   return k <= int8_bound_integers(entry_bits).kblock && nprimes >= 1;
 }
 
+// Without the residue form: the digit planes of one integer product, or beyond
+// one int32 block the reduced copies.
+size_t crt_digits_workspace(int64_t m, int64_t n, int64_t k, int entry_bits, int nprimes) {
+  const int d = crt_digits(entry_bits);
+  const size_t kp = (size_t)((k + 63) / 64 * 64);
+  if (crt_fast(k, entry_bits, nprimes)) return digit_planes_bytes(d, m, kp) + digit_planes_bytes(d, n, kp);
+  // fallback: per modulus, reduced A and B in binary64 (the products use the
+  // planner's form; an INT8 product needs at most 7-digit planes of A and B)
+  const size_t per = align_up(8 * (size_t)(m * k + k * n)) + align_up(int8_workspace_bytes(kMaxDigits, m, n, k));
+  return per * (size_t)nprimes;
+}
+
 }  // namespace
 
 extern "C" {
@@ -184,13 +196,9 @@ int mm_modp_batched(const mmp_job* jobs, int count, const mmp_opts* opts, void* 
 size_t mmp_workspace_crt(int64_t m, int64_t n, int64_t k, int entry_bits, int nprimes, const mmp_opts* opts) {
   (void)opts;
   if (m <= 0 || n <= 0 || k <= 0 || entry_bits < 1 || entry_bits > 62 || nprimes < 1) return 0;
-  const int d = crt_digits(entry_bits);
-  const size_t kp = (size_t)((k + 63) / 64 * 64);
-  if (crt_fast(k, entry_bits, nprimes)) return digit_planes_bytes(d, m, kp) + digit_planes_bytes(d, n, kp);
-  // fallback: per modulus, reduced A and B in binary64 (the products use the
-  // planner's form; an INT8 product needs at most 7-digit planes of A and B)
-  const size_t per = align_up(8 * (size_t)(m * k + k * n)) + align_up(int8_workspace_bytes(kMaxDigits, m, n, k));
-  return per * (size_t)nprimes;
+  RnsCrt rc;  // its planes do not depend on the primes
+  const size_t residues = rns_crt_plan(m, n, k, entry_bits, kPMax, &rc) ? rc.plan.bytes : 0;
+  return std::max(residues, crt_digits_workspace(m, n, k, entry_bits, nprimes));
 }
 
 int mm_modp_crt(const mmp_opts* opts, const uint64_t* A, int64_t lda, const uint64_t* B, int64_t ldb, int64_t m,
@@ -222,9 +230,20 @@ int mm_modp_crt(const mmp_opts* opts, const uint64_t* A, int64_t lda, const uint
       if (int st = validate_integer_entries(entry_bits, m, n, k, A, lda, B, ldb, stream)) return st;
 
     const int d = crt_digits(entry_bits);
-    const size_t ws = mmp_workspace_crt(m, n, k, entry_bits, nprimes, opts);
     void* work = nullptr;
     bool owned = false;
+    // the residue form where it is faster and its planes fit
+    RnsCrt rc;
+    if (rns_crt_chosen(m, n, k, entry_bits, primes, nprimes, opts, &rc) &&
+        (!opts || ((uintptr_t)opts->workspace % 16) == 0)) {
+      if (acquire_workspace(rc.plan.bytes, opts, stream, &work, &owned) == MMP_OK) {
+        const int st = hip_status(launch_rns_crt(rc, A, lda, B, ldb, m, n, k, primes, nprimes, C, ldc, work, stream));
+        const int st2 = release_workspace(work, owned, stream);
+        return st ? st : st2;
+      }
+      if (!(opts && opts->workspace)) (void)hipGetLastError();  // the launches below report their own
+    }
+    const size_t ws = crt_digits_workspace(m, n, k, entry_bits, nprimes);
     if (int st = acquire_workspace(ws, opts, stream, &work, &owned)) return st;
     int st = MMP_OK;
     if (crt_fast(k, entry_bits, nprimes)) {

@@ -207,6 +207,18 @@ int rns_moduli(double log2_bound);  // moduli for integers up to 2^log2_bound in
 // estimated faster in the residue form than on its digit planes.
 bool rns_chosen(uint64_t p, int64_t m, int64_t n, int64_t k, const mmp_opts* opts, RnsPlan* r);
 int launch_rns(const RnsPlan& r, const Int8Args& g, void* stream);
+// The multi-modular product in the same form: X in `limbs` limbs of base
+// 2^base_bits, which every prime reduces.
+struct RnsCrt {
+  RnsPlan plan;
+  int base_bits, limbs;
+};
+bool rns_crt_plan(int64_t m, int64_t n, int64_t k, int entry_bits, uint64_t smallest_prime, RnsCrt* c);
+bool rns_crt_chosen(int64_t m, int64_t n, int64_t k, int entry_bits, const uint64_t* primes, int nprimes,
+                    const mmp_opts* opts, RnsCrt* c);
+int launch_rns_crt(const RnsCrt& c, const uint64_t* A, int64_t lda, const uint64_t* B, int64_t ldb, int64_t m, int64_t n,
+                   int64_t k, const uint64_t* primes, int nprimes, double* const* C, int64_t ldc, void* work,
+                   void* stream);
 
 // Phase timer hooks (null tokens unless mmp_timers_enable(1)).  A launch
 // passes timer_start(t) / timer_stop(t) as the start and stop events of

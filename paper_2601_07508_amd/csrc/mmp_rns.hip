@@ -107,44 +107,77 @@ int current_cus() {
   return cus;
 }
 
+// Residue planes of both operands.  WIDE: entries of more than 4 digits.
+template <class In, bool WIDE>
+int launch_convert(const RnsPlan& r, const In& A, int64_t m, int64_t lda, const In& B, int64_t n, int64_t ldb,
+                   int64_t k, int8_t* planes, hipStream_t s) {
+  using namespace rns;
+  ConvArgs ca;
+  ca.n = r.n;
+  std::memcpy(ca.c, tables().conv, sizeof(ca.c));
+  const int64_t kp = cdiv(k, 64) * 64;
+  const int64_t na = row_blocks(m) * cdiv(kp, 256), nb = cdiv(n, 64) * (kp / 64);
+  // moduli in up to four parts while the grid is under four workgroups a CU
+  unsigned parts = 1;
+  while (parts < 4 && (na + nb) * parts < 1024) parts *= 2;
+  TimerTok* t = timer_begin("rns_convert");
+  hipExtLaunchKernelGGL((rns_convert_kernel<In, WIDE>), dim3((unsigned)(na + nb), parts), dim3(256), 0, s,
+                        timer_start(t), timer_stop(t), 0, ca, A, m, lda, B, n, ldb, k, kp, planes, planes + r.bytes_a,
+                        na);
+  const int e = (int)hipGetLastError();
+  timer_commit(t, e);
+  return e;
+}
+
+// The INT8 products, and where their residues lie.
 template <class S>
-int launch_products(const RnsPlan& r, const Int8Args& g, int8_t* planes, hipStream_t s) {
+int launch_products(const RnsPlan& r, int64_t m, int64_t n, int64_t k, int8_t* planes, hipStream_t s, rns::RnsOut* o) {
   using namespace rns;
   RnsGemmArgs a;
   std::memset(&a, 0, sizeof(a));
   a.Ad = planes;
   a.Bd = planes + r.bytes_a;
   a.res = planes + r.bytes_a + r.bytes_b;
-  a.kp = g.kp;
-  a.ablk = (int)row_blocks(g.m);
-  a.bblk = (int)row_blocks(g.n);
-  a.tiles_m = (int)cdiv(g.m, S::BM);
-  a.tiles_n = (int)cdiv(g.n, S::BN);
+  a.kp = cdiv(k, 64) * 64;
+  a.ablk = (int)row_blocks(m);
+  a.bblk = (int)row_blocks(n);
+  a.tiles_m = (int)cdiv(m, S::BM);
+  a.tiles_n = (int)cdiv(n, S::BN);
   a.n = r.n;
   a.splits = r.splits;
-  a.stages = (int)(g.kp / 64);
+  a.stages = (int)(a.kp / 64);
   a.per_split = (int)cdiv(a.stages, r.splits);
   std::memcpy(a.c, tables().gemm, sizeof(a.c));
-  const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n, items = tiles * r.n * r.splits;
+  const int64_t items = (int64_t)a.tiles_m * a.tiles_n * r.n * r.splits;
   const int64_t grid = std::min<int64_t>(items, (int64_t)current_cus() * S::GROUPS);
   TimerTok* t = timer_begin("rns_gemm");
   hipExtLaunchKernelGGL((rns_gemm_kernel<S>), dim3((unsigned)grid), dim3(S::THREADS), 0, s, timer_start(t),
                         timer_stop(t), 0, a);
-  int e = (int)hipGetLastError();
+  const int e = (int)hipGetLastError();
   timer_commit(t, e);
-  if (e) return e;
+  o->res = a.res;
+  o->m = m;
+  o->n = n;
+  o->tiles_m = a.tiles_m;
+  o->tiles_n = a.tiles_n;
+  o->nmod = r.n;
+  o->splits = r.splits;
+  return e;
+}
 
+template <class S>
+int64_t units_of(const rns::RnsOut& o) {
+  return (int64_t)o.tiles_m * o.tiles_n * S::NW * S::XB * S::YB / 4;
+}
+
+template <class S>
+int launch_mod_p(const RnsPlan& r, const Int8Args& g, int8_t* planes, hipStream_t s) {
+  using namespace rns;
   CombineArgs b;
   std::memset(&b, 0, sizeof(b));
-  b.res = a.res;
+  if (int e = launch_products<S>(r, g.m, g.n, g.k, planes, s, &b.o)) return e;
+  b.o.ldc = g.ldc;
   b.C = g.C;
-  b.m = g.m;
-  b.n = g.n;
-  b.ldc = g.ldc;
-  b.tiles_m = a.tiles_m;
-  b.tiles_n = a.tiles_n;
-  b.nmod = r.n;
-  b.splits = r.splits;
   b.p = (double)g.p;
   b.q = g.q;
   // M / m_t mod p as the product of the moduli before t and those after it
@@ -159,13 +192,108 @@ int launch_products(const RnsPlan& r, const Int8Args& g, int8_t* planes, hipStre
     b.f[i] = (double)inv / (double)kModuli[i];
     before = mulmod_u64(before, (uint64_t)kModuli[i], g.p);
   }
-  const int64_t units = tiles * S::NW * S::XB * S::YB / 4;
-  t = timer_begin("rns_combine");
-  hipExtLaunchKernelGGL((rns_combine_kernel<S>), dim3((unsigned)cdiv(units, 4)), dim3(256), 0, s, timer_start(t),
-                        timer_stop(t), 0, b);
-  e = (int)hipGetLastError();
+  TimerTok* t = timer_begin("rns_combine");
+  hipExtLaunchKernelGGL((rns_combine_kernel<S>), dim3((unsigned)cdiv(units_of<S>(b.o), 4)), dim3(256), 0, s,
+                        timer_start(t), timer_stop(t), 0, b);
+  const int e = (int)hipGetLastError();
   timer_commit(t, e);
   return e;
+}
+
+// Integers of up to 192 bits, two's complement, as 32-bit words: W_t and M.
+struct Wide {
+  static constexpr int kWords = 6;
+  uint32_t w[kWords] = {1, 0, 0, 0, 0, 0};
+  void mul(uint32_t x) {
+    uint64_t c = 0;
+    for (int i = 0; i < kWords; i++) {
+      c += (uint64_t)w[i] * x;
+      w[i] = (uint32_t)c;
+      c >>= 32;
+    }
+  }
+  void negate() {
+    uint64_t c = 1;
+    for (int i = 0; i < kWords; i++) {
+      c += (uint32_t)~w[i];
+      w[i] = (uint32_t)c;
+      c >>= 32;
+    }
+  }
+  // limbs of base 2^b, all but the top in [0, 2^b)
+  void limbs(int b, int n, double* out) const {
+    for (int j = 0; j < n; j++) {
+      unsigned __int128 v = 0;
+      const int bit = j * b;
+      for (int i = bit / 32, s = -(bit % 32); i < kWords && s < 64; i++, s += 32)
+        v |= s >= 0 ? (unsigned __int128)w[i] << s : (unsigned __int128)(w[i] >> -s);
+      if (j + 1 < n) {
+        out[j] = (double)(uint64_t)(v & (((uint64_t)1 << b) - 1));
+      } else {  // sign-extended from 192 bits
+        const int left = 32 * kWords - bit;
+        int64_t x = (int64_t)(uint64_t)v;
+        if (left < 64) x = (int64_t)((uint64_t)x << (64 - left)) >> (64 - left);
+        out[j] = (double)x;
+      }
+    }
+  }
+};
+
+template <class S, int NG>
+int launch_primes(const rns::CrtCombineArgs& b, hipStream_t s) {
+  TimerTok* t = timer_begin("rns_crt_combine");
+  hipExtLaunchKernelGGL((rns::rns_crt_combine_kernel<S, NG>), dim3((unsigned)cdiv(2 * units_of<S>(b.o), 4)), dim3(256),
+                        0, s, timer_start(t), timer_stop(t), 0, b);
+  const int e = (int)hipGetLastError();
+  timer_commit(t, e);
+  return e;
+}
+
+template <class S>
+int launch_crt_shape(const RnsCrt& c, const uint64_t* primes, int nprimes, double* const* C, int64_t ldc, int64_t m,
+                     int64_t n, int64_t k, int8_t* planes, hipStream_t s) {
+  using namespace rns;
+  const RnsPlan& r = c.plan;
+  CrtCombineArgs b;
+  std::memset(&b, 0, sizeof(b));
+  if (int e = launch_products<S>(r, m, n, k, planes, s, &b.o)) return e;
+  b.o.ldc = ldc;
+  b.base = std::ldexp(1.0, c.base_bits);
+  b.rbase = std::ldexp(1.0, -c.base_bits);
+  Wide M;
+  for (int i = 0; i < r.n; i++) M.mul((uint32_t)kModuli[i]);
+  M.limbs(c.base_bits, c.limbs, b.M);
+  for (int i = 0; i < r.n; i++) {
+    const int inv = tables().inv[r.n][i];
+    Wide W;
+    for (int j = 0; j < r.n; j++)
+      if (j != i) W.mul((uint32_t)kModuli[j]);
+    W.mul((uint32_t)std::abs(inv));
+    if (inv < 0) W.negate();
+    W.limbs(c.base_bits, c.limbs, b.w[i]);
+    b.f[i] = (double)inv / (double)kModuli[i];
+  }
+  for (int i0 = 0; i0 < nprimes; i0 += kMaxPrimesCrt) {
+    b.nprimes = std::min(kMaxPrimesCrt, nprimes - i0);
+    b.lines = ldc % 16 == 0;
+    for (int i = 0; i < b.nprimes; i++) {
+      b.p[i] = (double)primes[i0 + i];
+      b.q[i] = 1.0 / (double)primes[i0 + i];
+      b.C[i] = C[i0 + i];
+      if ((uintptr_t)b.C[i] % 128) b.lines = 0;
+    }
+    int e;
+    switch (c.limbs) {
+      case 1: e = launch_primes<S, 1>(b, s); break;
+      case 2: e = launch_primes<S, 2>(b, s); break;
+      case 3: e = launch_primes<S, 3>(b, s); break;
+      case 4: e = launch_primes<S, 4>(b, s); break;
+      case 5: e = launch_primes<S, 5>(b, s); break;
+      default: e = launch_primes<S, 6>(b, s); break;
+    }
+    if (e) return e;
+  }
+  return 0;
 }
 
 }  // namespace
@@ -269,27 +397,73 @@ bool rns_chosen(uint64_t p, int64_t m, int64_t n, int64_t k, const mmp_opts* opt
 int launch_rns(const RnsPlan& r, const Int8Args& g, void* stream) {
   using namespace rns;
   hipStream_t s = (hipStream_t)stream;
-  int8_t* planes = g.work;
-  ConvArgs ca;
-  ca.n = r.n;
-  std::memcpy(ca.c, tables().conv, sizeof(ca.c));
   const CenteredIn A{g.A, (int64_t)g.p, (int64_t)(g.p / 2)}, B{g.B, (int64_t)g.p, (int64_t)(g.p / 2)};
-  const int64_t na = row_blocks(g.m) * cdiv(g.kp, 256), nb = cdiv(g.n, 64) * (g.kp / 64);
-  // moduli in up to four parts while the grid is under four workgroups a CU
-  unsigned parts = 1;
-  while (parts < 4 && (na + nb) * parts < 1024) parts *= 2;
-  const dim3 grid((unsigned)(na + nb), parts);
-  TimerTok* t = timer_begin("rns_convert");
-  if (g.p >> 31)
-    hipExtLaunchKernelGGL((rns_convert_kernel<CenteredIn, true>), grid, dim3(256), 0, s, timer_start(t), timer_stop(t), 0, ca, A, g.m, g.lda, B, g.n, g.ldb, g.k, g.kp, planes,
-                          planes + r.bytes_a, na);
-  else
-    hipExtLaunchKernelGGL((rns_convert_kernel<CenteredIn, false>), grid, dim3(256), 0, s, timer_start(t), timer_stop(t), 0, ca, A, g.m, g.lda, B, g.n, g.ldb, g.k, g.kp, planes,
-                          planes + r.bytes_a, na);
-  const int e = (int)hipGetLastError();
-  timer_commit(t, e);
+  const int e = g.p >> 31 ? launch_convert<CenteredIn, true>(r, A, g.m, g.lda, B, g.n, g.ldb, g.k, g.work, s)
+                          : launch_convert<CenteredIn, false>(r, A, g.m, g.lda, B, g.n, g.ldb, g.k, g.work, s);
   if (e) return e;
-  return r.large ? launch_products<RnsLarge>(r, g, planes, s) : launch_products<RnsSmall>(r, g, planes, s);
+  return r.large ? launch_mod_p<RnsLarge>(r, g, g.work, s) : launch_mod_p<RnsSmall>(r, g, g.work, s);
+}
+
+// The multi-modular product of integers below 2^entry_bits: 0 <= X <
+// k 2^(2 entry_bits).
+bool rns_crt_plan(int64_t m, int64_t n, int64_t k, int entry_bits, uint64_t smallest_prime, RnsCrt* c) {
+  using namespace rns;
+  if (m <= 0 || n <= 0 || k <= 0 || std::max(std::max(m, n), k) > 0x7fffffff) return false;
+  const double bits = std::log2((double)k) + 2.0 * entry_bits;
+  const int nm = rns_moduli(bits);
+  if (nm == 0) return false;
+  RnsPlan small, large;
+  if (!plan_shape<RnsSmall>(nm, m, n, k, &small)) return false;
+  c->plan = small;
+  if (plan_shape<RnsLarge>(nm, m, n, k, &large) && large.us < small.us) c->plan = large;
+  if (c->plan.bytes > kRnsMaxBytes) return false;
+  // the base: 2^b (1 + 2^b / p) <= 2^50 for every prime, limbs below 2^53 before
+  // their carries (20 moduli, 128, the k-ranges)
+  int b = 24;
+  while (b < 40 && std::ldexp(1.0, 2 * (b + 1)) / (double)smallest_prime + std::ldexp(1.0, b + 1) <= std::ldexp(1.0, 50) &&
+         std::ldexp(1.0, b + 1) * 2 * 20 * 128 * c->plan.splits < std::ldexp(1.0, 53))
+    b++;
+  // the limbs hold M, and with it every W_t
+  const double mbits = tables().log2M[nm] + 1.0;
+  const int limbs = (int)std::ceil(mbits / b);
+  if (limbs > kCrtLimbs) return false;
+  c->base_bits = (int)std::ceil(mbits / limbs);  // no wider than it needs to be
+  c->limbs = limbs;
+  return true;
+}
+
+bool rns_crt_chosen(int64_t m, int64_t n, int64_t k, int entry_bits, const uint64_t* primes, int nprimes,
+                    const mmp_opts* opts, RnsCrt* c) {
+  if (opts && opts->form != MMP_FORM_AUTO) return false;
+  if (!rns_crt_plan(m, n, k, entry_bits, *std::min_element(primes, primes + nprimes), c)) return false;
+  // Beyond one int32 block the alternative is a product per prime.
+  if (k > int8_bound_integers(entry_bits).kblock) return true;
+  // Else the digit form's one kernel for the D^2 digit products and all primes.
+  // Both in microseconds, fitted to 300 jobs with m, n log-uniform up to 3072,
+  // k to 8192, 16 to 62 bits and 3 to 64 primes (within 18% for 80% of them;
+  // choosing by it costs 1.2% over always choosing right).  The residue form
+  // won 214 of them (2048^3, 60 bits, 32 primes: 666 -> 445 us); short k with
+  // few bits stays with the digits (2521 x 2750 x 263, 32 bits, 5 primes: 164
+  // against 190).
+  const int D = crt_digits(entry_bits);
+  const double entries = ((double)m + n) * k, out = 8e-6 * (double)m * n * nprimes, chain = (double)cdiv(k, 64) * D * D;
+  const int64_t tiles = cdiv(m, 64) * cdiv(n, 64), rounds = cdiv(tiles, D <= 5 ? 512 : 256);
+  const double digits = 12.5 + 0.22e-6 * entries * (8 + D) + 0.0092 * (double)tiles * chain / 512 +
+                        0.037 * (double)rounds * chain + 0.79 * (double)rounds * nprimes + 0.231 * out;
+  const int64_t waves = 32 * cdiv(m, 128) * cdiv(n, 128);
+  const double residues = 0.7 + 0.894 * c->plan.us + 0.139 * out + nprimes * (0.464 + 0.2 * (double)cdiv(waves, 1024));
+  return residues < digits;
+}
+
+int launch_rns_crt(const RnsCrt& c, const uint64_t* A, int64_t lda, const uint64_t* B, int64_t ldb, int64_t m, int64_t n,
+                   int64_t k, const uint64_t* primes, int nprimes, double* const* C, int64_t ldc, void* work,
+                   void* stream) {
+  using namespace rns;
+  hipStream_t s = (hipStream_t)stream;
+  int8_t* planes = (int8_t*)work;
+  if (int e = launch_convert<IntegerIn, true>(c.plan, IntegerIn{A}, m, lda, IntegerIn{B}, n, ldb, k, planes, s)) return e;
+  return c.plan.large ? launch_crt_shape<RnsLarge>(c, primes, nprimes, C, ldc, m, n, k, planes, s)
+                      : launch_crt_shape<RnsSmall>(c, primes, nprimes, C, ldc, m, n, k, planes, s);
 }
 
 }  // namespace mmp

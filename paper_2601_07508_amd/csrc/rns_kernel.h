@@ -405,10 +405,10 @@ __global__ __launch_bounds__(S::THREADS, S::THREADS *S::GROUPS / 256) void rns_g
       }
 #pragma unroll
       for (int e = i * (CA + CB) / XB; e < (i + 1) * (CA + CB) / XB; e++) copy(e, fill);
-      // B's fragment first: a lane's four outputs are then consecutive columns
+      // output layout: a lane holds four consecutive rows of column lane & 15
 #pragma unroll
       for (int j = 0; j < YB; j++)
-        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(b0[j], af[i], acc[i][j], 0, 0, 0);
+        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[i], b0[j], acc[i][j], 0, 0, 0);
     }
     // keep that order: a group's reads and copies between its MFMAs
 #pragma unroll
@@ -478,11 +478,86 @@ __global__ __launch_bounds__(S::THREADS, S::THREADS *S::GROUPS / 256) void rns_g
 
 // ---------------------------------------------------------------- recombination
 
-struct CombineArgs {
+// Where a wave's outputs lie: unit u of a tile is 16 rows by 64 columns, 1 KB of
+// residue bytes per modulus and k-range.  Lane 16 g + c holds, in word y, rows
+// 4 g .. 4 g + 3 of column 16 y + c: a store over the lanes writes whole 128-byte
+// pieces of four rows.
+struct RnsOut {
   const int8_t* res;
-  double* C;
   int64_t m, n, ldc;
   int tiles_m, tiles_n, nmod, splits;
+};
+struct Unit {
+  const int8_t* src;
+  int64_t step;  // to the next (modulus, k-range)
+  int64_t row, col;
+  bool any;      // part of the unit lies inside the output
+};
+template <class S>
+__device__ __forceinline__ Unit unit_of(const RnsOut& a, int64_t unit, int lane) {
+  constexpr int UNITS = S::NW * S::XB * S::YB / 4;
+  const int tiles = a.tiles_m * a.tiles_n;
+  const int tile = (int)(unit / UNITS), u = (int)(unit % UNITS);
+  const int group = 8 * a.tiles_n, gid = tile / group, first = gid * 8;
+  const int gm = min(a.tiles_m - first, 8), in = tile - gid * group;
+  const int tm = first + in % gm, tn = in / gm;
+  const int w = u / (S::XB * S::YB / 4), x = u % (S::XB * S::YB / 4) / (S::YB / 4), y4 = u % (S::YB / 4);
+  const int64_t row0 = (int64_t)tm * S::BM + ((w / S::WN) * S::XB + x) * 16;
+  const int64_t col0 = (int64_t)tn * S::BN + (w % S::WN) * S::YB * 16 + y4 * 64;
+  Unit r;
+  r.src = a.res + (int64_t)tile * S::TILE_BYTES + u * 1024 + lane * 16;
+  r.step = (int64_t)tiles * S::TILE_BYTES;
+  r.row = row0 + (lane >> 4) * 4;
+  r.col = col0 + (lane & 15);
+  r.any = row0 < a.m && col0 < a.n;  // uniform
+  return r;
+}
+
+// Feeds add(r, t) the residues mod m_t of this lane's 4 W outputs (summed over
+// the k-ranges), W words a (modulus, k-range) pair from `src` on, with kLoads
+// pairs in flight.
+template <int W, class Add>
+__device__ __forceinline__ void each_modulus(const int8_t* src, int64_t step, int nmod, int splits, Add add) {
+  typedef int words __attribute__((ext_vector_type(W)));
+  constexpr int kLoads = 8;
+  const int total = nmod * splits;
+  words v[kLoads];
+#pragma unroll
+  for (int i = 0; i < kLoads; i++) v[i] = __builtin_nontemporal_load((const words*)(src + min(i, total - 1) * step));
+  int sum[4 * W];
+  int t = 0, s = 0;
+  for (int j = 0; j < total; j += kLoads) {
+    words w[kLoads];
+#pragma unroll
+    for (int i = 0; i < kLoads; i++) w[i] = v[i];
+    if (j + kLoads < total) {
+#pragma unroll
+      for (int i = 0; i < kLoads; i++)
+        v[i] = __builtin_nontemporal_load((const words*)(src + min(j + kLoads + i, total - 1) * step));
+    }
+#pragma unroll
+    for (int h = 0; h < kLoads; h++) {
+      if (j + h >= total) break;  // uniform
+      int r[4 * W];
+#pragma unroll
+      for (int i = 0; i < 4 * W; i++) r[i] = (int)(int8_t)(w[h][i / 4] >> (8 * (i % 4)));
+      if (splits == 1) {
+        add(r, j + h);
+        continue;
+      }
+#pragma unroll
+      for (int i = 0; i < 4 * W; i++) sum[i] = s == 0 ? r[i] : sum[i] + r[i];
+      if (++s == splits) {
+        add(sum, t++);
+        s = 0;
+      }
+    }
+  }
+}
+
+struct CombineArgs {
+  RnsOut o;
+  double* C;
   double p, q;
   double mhi, mlo;  // M mod p as mhi 2^26 + mlo
   double whi[kRnsMaxModuli], wlo[kRnsMaxModuli];  // W_t mod p as whi 2^26 + wlo
@@ -503,30 +578,20 @@ __device__ __forceinline__ double reduce_near(double x, double p, double q) {
 // all exact, and X = 2^26 hi + lo mod p.  hi is reduced to p/2 + 1 of zero,
 // 2^26 times that is exact (a power of two) and its quotient is below 2^26.1,
 // so it reduces to p/2 + 1 of zero again; adding lo stays below 2^53 and one
-// complete Alg. 1 ends it.
+// complete Alg. 1 ends it.  Bound by memory: N bytes read and 8 written an output,
+// 5.1 TB/s at 8192^2 outputs and 15 moduli.
 constexpr int kOutRow = 66;
 template <class S>
 __global__ __launch_bounds__(256) void rns_combine_kernel(const CombineArgs a) {
-  __shared__ __attribute__((aligned(16))) double lds[4][16 * kOutRow];
+  __shared__ double lds[4][16 * kOutRow];
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  constexpr int UNITS = S::NW * S::XB * S::YB / 4;  // 16-row by 64-column units of a tile, one per wave here
-  const int64_t unit = (int64_t)blockIdx.x * 4 + wv;
-  const int tiles = a.tiles_m * a.tiles_n;
-  const int tile = (int)(unit / UNITS), u = (int)(unit % UNITS);
-  const int group = 8 * a.tiles_n, gid = tile / group, first = gid * 8;
-  const int gm = min(a.tiles_m - first, 8), in = tile - gid * group;
-  const int tm = first + in % gm, tn = in / gm;
-  const int w = u / (S::XB * S::YB / 4), x = u % (S::XB * S::YB / 4) / (S::YB / 4), y4 = u % (S::YB / 4);
-  const int64_t row = (int64_t)tm * S::BM + ((w / S::WN) * S::XB + x) * 16 + (lane & 15);
-  const int64_t col0 = (int64_t)tn * S::BN + (w % S::WN) * S::YB * 16 + y4 * 64 + (lane >> 4) * 4;
-  if (row - (lane & 15) >= a.m || col0 - (lane >> 4) * 4 >= a.n) return;  // uniform: nothing of C here
-  const int8_t* src = a.res + (int64_t)tile * S::TILE_BYTES + u * 1024 + lane * 16;
-  const int64_t step = (int64_t)tiles * S::TILE_BYTES;
+  const Unit u = unit_of<S>(a.o, (int64_t)blockIdx.x * 4 + wv, lane);
+  if (!u.any) return;
   double hi[16], lo[16], g[16];
 #pragma unroll
   for (int i = 0; i < 16; i++) hi[i] = lo[i] = g[i] = 0.0;
-  auto add = [&](const int (&r)[16], int t) {
+  each_modulus<4>(u.src, u.step, a.o.nmod, a.o.splits, [&](const int (&r)[16], int t) {
     const double wh = a.whi[t], wl = a.wlo[t], f = a.f[t];
 #pragma unroll
     for (int i = 0; i < 16; i++) {
@@ -535,64 +600,136 @@ __global__ __launch_bounds__(256) void rns_combine_kernel(const CombineArgs a) {
       lo[i] = fma(d, wl, lo[i]);
       g[i] = fma(d, f, g[i]);
     }
-  };
-  auto bytes = [](const int4v& v, int (&r)[16]) {
-#pragma unroll
-    for (int i = 0; i < 16; i++) r[i] = (int)(int8_t)(v[i / 4] >> (8 * (i % 4)));
-  };
-  // the bytes of all (modulus, k-range) pairs in order, kLoads of them in flight
-  constexpr int kLoads = 8;
-  const int total = a.nmod * a.splits;
-  int4v v[kLoads];
-#pragma unroll
-  for (int i = 0; i < kLoads; i++) v[i] = __builtin_nontemporal_load((const int4v*)(src + min(i, total - 1) * step));
-  int sum[16];
-  int t = 0, s = 0;
-  for (int j = 0; j < total; j += kLoads) {
-    int4v w[kLoads];
-#pragma unroll
-    for (int i = 0; i < kLoads; i++) w[i] = v[i];
-    if (j + kLoads < total) {
-#pragma unroll
-      for (int i = 0; i < kLoads; i++)
-        v[i] = __builtin_nontemporal_load((const int4v*)(src + min(j + kLoads + i, total - 1) * step));
-    }
-#pragma unroll
-    for (int h = 0; h < kLoads; h++) {
-      if (j + h >= total) break;  // uniform
-      int r[16];
-      bytes(w[h], r);
-      if (a.splits == 1) {
-        add(r, j + h);
-        continue;
-      }
-#pragma unroll
-      for (int i = 0; i < 16; i++) sum[i] = s == 0 ? r[i] : sum[i] + r[i];
-      if (++s == a.splits) {
-        add(sum, t++);
-        s = 0;
-      }
-    }
-  }
+  });
   const double p = a.p, q = a.q;
-  double* const mine = lds[wv] + (lane & 15) * kOutRow + (lane >> 4) * 4;
 #pragma unroll
-  for (int i = 0; i < 16; i++) {
-    const double h = rint(g[i]);
-    const double H = fma(-h, a.mhi, hi[i]), L = fma(-h, a.mlo, lo[i]);
-    const double t = reduce_near(67108864.0 * reduce_near(H, p, q), p, q) + L;
-    double d = fma(-floor(t * q), p, t);
-    d = (d >= p) ? d - p : d;
-    d = (d < 0.0) ? d + p : d;
-    mine[16 * (i / 4) + i % 4] = d + 0.0;  // +0.0: canonical zero
-  }
+  for (int y = 0; y < 4; y++)
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const int i = 4 * y + e;
+      const double h = rint(g[i]);
+      const double H = fma(-h, a.mhi, hi[i]), L = fma(-h, a.mlo, lo[i]);
+      const double t = reduce_near(67108864.0 * reduce_near(H, p, q), p, q) + L;
+      double d = fma(-floor(t * q), p, t);
+      d = (d >= p) ? d - p : d;
+      d = (d < 0.0) ? d + p : d;
+      lds[wv][((lane >> 4) * 4 + e) * kOutRow + 16 * y + (lane & 15)] = d + 0.0;  // +0.0: canonical zero
+    }
   __builtin_amdgcn_wave_barrier();
-  // whole rows of 64 columns, 512 contiguous bytes a store whatever C's alignment
-  const int64_t row0 = row - (lane & 15), col = col0 - (lane >> 4) * 4 + lane;
-  const int rows = (int)min((int64_t)16, a.m - row0);
-  double* out = a.C + row0 * a.ldc + col;
-  if (col < a.n)
-    for (int r = 0; r < rows; r++) __builtin_nontemporal_store(lds[wv][r * kOutRow + lane], out + r * a.ldc);
+  // whole rows of 64 columns, 512 contiguous bytes a store (stores of the lanes'
+  // own values, four pieces of 128 bytes, took 74 us at 4096^2 outputs against
+  // 62), and not streaming ones: on rows that start inside a cache line those
+  // write parts of lines to memory (6001 x 5003: 552 us against 160).
+  const int64_t row0 = u.row - (lane >> 4) * 4, col = u.col - (lane & 15) + lane;
+  const int rows = (int)min((int64_t)16, a.o.m - row0);
+  double* const out = a.C + row0 * a.o.ldc + col;
+  if (col < a.o.n)
+    for (int r = 0; r < rows; r++) __builtin_nontemporal_store(lds[wv][r * kOutRow + lane], out + r * a.o.ldc);
+}
+
+// The multi-modular product's recombination: the same residues, of products of
+// integers in [0, 2^62), into X itself as NG limbs of base 2^b, and each of up
+// to 64 primes reduces those.
+constexpr int kCrtLimbs = 6;
+struct CrtCombineArgs {
+  RnsOut o;
+  int nprimes;
+  int lines;           // every C's rows start on 128-byte lines
+  double base, rbase;  // 2^b, 2^-b
+  double f[kRnsMaxModuli], w[kRnsMaxModuli][kCrtLimbs], M[kCrtLimbs];
+  double p[kMaxPrimesCrt], q[kMaxPrimesCrt];
+  double* C[kMaxPrimesCrt];
+};
+
+// Limb j of X is sum_t r_t W_t,j - h M_j (the top limb of W_t signed, the others
+// in [0, 2^b)), below 20 64 2^7 2^b + 2^17 2^b; the launcher keeps that below
+// 2^53.  Carries rounded to nearest leave |limb| <= 2^(b-1) + 1, the top one
+// below 2^b.  Per prime, Horner's rule with the base 2^b over the limbs as they
+// are: |t| <= p + 2^b at every step and the quotient argument 2^b (1 + 2^b / p)
+// stays below 2^50 (launcher), so its error is below 1/4, the reduced value lies
+// within 3/4 p + 1 of zero and every step is exact; the last reduction's quotient
+// is below 2^26, which leaves it within p/2 + 1 of zero, and adding p to a
+// negative one ends it.  Bound by the primes' outputs: 32 of them at 2048^2 are
+// 1.07 GB.
+constexpr int kCrtRow = 34;
+template <class S, int NG>
+__global__ __launch_bounds__(256) void rns_crt_combine_kernel(const CrtCombineArgs a) {
+  __shared__ double lds[4][16 * kCrtRow];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // a wave takes half a unit, two of the four words: its limbs then leave
+  // registers for two waves a SIMD and more
+  const int64_t id = (int64_t)blockIdx.x * 4 + wv;
+  const int half = (int)(id & 1);
+  const Unit u = unit_of<S>(a.o, id >> 1, lane);
+  const int64_t col = u.col + 32 * half;
+  if (!u.any || col - (lane & 15) >= a.o.n) return;
+  double g[8], G[8][NG];
+#pragma unroll
+  for (int i = 0; i < 8; i++) {
+    g[i] = 0.0;
+#pragma unroll
+    for (int j = 0; j < NG; j++) G[i][j] = 0.0;
+  }
+  each_modulus<2>(u.src + 8 * half, u.step, a.o.nmod, a.o.splits, [&](const int (&r)[8], int t) {
+    const double f = a.f[t];
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+      const double d = (double)r[i];
+      g[i] = fma(d, f, g[i]);
+#pragma unroll
+      for (int j = 0; j < NG; j++) G[i][j] = fma(d, a.w[t][j], G[i][j]);
+    }
+  });
+  const double base = a.base, rbase = a.rbase;
+#pragma unroll
+  for (int i = 0; i < 8; i++) {
+    const double h = rint(g[i]);
+#pragma unroll
+    for (int j = 0; j < NG; j++) G[i][j] = fma(-h, a.M[j], G[i][j]);
+#pragma unroll
+    for (int j = 0; j + 1 < NG; j++) {
+      const double c = rint(G[i][j] * rbase);
+      G[i][j] = fma(-c, base, G[i][j]);
+      G[i][j + 1] += c;
+    }
+  }
+  // stores as in rns_combine_kernel, two rows of 32 columns at a time
+  const int64_t row0 = u.row - (lane >> 4) * 4 + (lane >> 5), col0 = col - (lane & 15) + (lane & 31);
+  const int rows = col0 < a.o.n ? (int)min((int64_t)16, a.o.m - row0) : 0;
+  const int64_t off = row0 * a.o.ldc + col0;
+  for (int pi = 0; pi < a.nprimes; pi++) {
+    const double p = a.p[pi], q = a.q[pi];
+    double* const out = a.C[pi] + off;
+#pragma unroll
+    for (int y = 0; y < 2; y++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        const int i = 4 * y + e;
+        double t = G[i][NG - 1];
+#pragma unroll
+        for (int j = NG - 2; j >= 0; j--) t = reduce_near(base * t, p, q) + G[i][j];
+        const double d = reduce_near(t, p, q);
+        lds[wv][((lane >> 4) * 4 + e) * kCrtRow + 16 * y + (lane & 15)] = (d < 0.0 ? d + p : d) + 0.0;
+      }
+    __builtin_amdgcn_wave_barrier();
+    double v[8];
+#pragma unroll
+    for (int r = 0; r < 8; r++) v[r] = lds[wv][(2 * r + (lane >> 5)) * kCrtRow + (lane & 31)];
+    // streaming stores where rows start on cache lines (32 primes at 2048^2: 231 us
+    // against 244); on others they write parts of lines to memory (2521 x 2750, 5
+    // primes: 131 us against 97)
+    if (a.lines) {
+#pragma unroll
+      for (int r = 0; r < 8; r++)
+        if (2 * r < rows) __builtin_nontemporal_store(v[r], out + 2 * r * a.o.ldc);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 8; r++)
+        if (2 * r < rows) out[2 * r * a.o.ldc] = v[r];
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
 }
 
 }  // namespace rns

@@ -146,3 +146,37 @@ def test_captured_in_a_graph():
         g.replay()
         torch.cuda.synchronize()
         assert np.array_equal(C.cpu().numpy(), oracle.mm_modp(p, A, B).astype(np.float64))
+
+
+def exact_mod(A, B, p):
+    """A B mod p of Python-integer-sized entries, row by row (the oracle reduces them first)."""
+    return oracle.mm_modp(p, A, B).astype(np.float64)
+
+
+# limbs: one (8-bit entries) to several; a prime of 5 forces the narrow base;
+# k beyond one int32 block of the digit form; more than 64 primes; odd and
+# line-aligned leading dimensions
+@pytest.mark.parametrize("m,n,k,bits,small,count,pad", [
+    (130, 257, 520, 62, [], 3, 0), (300, 200, 1000, 62, [5, 7], 6, 1), (260, 140, 4000, 8, [], 3, 0),
+    (64, 48, 30000, 60, [], 4, 0), (96, 80, 70000, 62, [11], 3, 1), (200, 144, 900, 33, [], 66, 0),
+    (513, 257, 1400, 47, [], 9, 0), (100, 90, 140000, 20, [], 3, 0),
+])
+def test_multi_modular(m, n, k, bits, small, count, pad):
+    primes = small + gen.crt_primes(count=count - len(small))
+    A = gen.uniform_bits(m, 1, m * k, bits).reshape(m, k)
+    B = gen.uniform_bits(n, 2, k * n, bits).reshape(k, n)
+    A[0, :] = B[:, 0] = (1 << bits) - 1  # the largest sum
+    A[1, :] = 0
+    say("multi-modular", m, n, k, bits, count, pad)
+    dA = torch.from_numpy(A.astype(np.int64)).cuda()
+    dB = torch.from_numpy(B.astype(np.int64)).cuda()
+    stores = [torch.full((m + 1, n + pad), -1.0, dtype=torch.float64, device="cuda") for _ in primes]
+    outs = [s[:m, :n] for s in stores]
+    phases = timed(lambda: mmp.mm_modp_crt(dA, dB, primes, outs, bits))
+    say(sorted(phases))
+    for p, s in zip(primes, stores):
+        got = s.cpu().numpy()
+        assert np.array_equal(got[:m, :n], exact_mod(A, B, p)), p
+        assert (got[m:] == -1.0).all() and (got[:, n:] == -1.0).all()
+    if (m, k) in ((130, 520), (300, 1000), (64, 30000), (96, 70000), (100, 140000)):
+        assert "rns_crt_combine" in phases, phases
