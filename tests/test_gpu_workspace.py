@@ -1,0 +1,74 @@
+"""Workspaces kept between calls: results stay exact when calls of different
+sizes share them over several streams and threads, and beside a graph capture."""
+import sys
+import threading
+
+import numpy as np
+import pytest
+
+import mmp_inputs as gen
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+mmp = pytest.importorskip("paper_2601_07508_amd")
+
+# products that need a workspace: digit planes, residue planes, split-K residues
+SHAPES = [(4503599627370449, 90, 70, 9000, {}), (1125899906842597, 513, 520, 2048, {}),
+          (68719476731, 300, 200, 700, {"form": mmp.FORM_INT8_WORDS}),
+          (8388593, 64, 64, 40000, {"form": mmp.FORM_FP64_WORDS})]
+
+
+def say(*a):
+    print(*a, file=sys.stderr, flush=True)
+
+
+@pytest.fixture(scope="module")
+def problems():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    out = []
+    for i, (p, m, n, k, kw) in enumerate(SHAPES):
+        A = gen.random_matrix(i, 1, m, k, p)
+        B = gen.random_matrix(i, 2, k, n, p)
+        want = torch.from_numpy(oracle.mm_modp(p, A, B).astype(np.float64)).cuda()
+        out.append((p, torch.from_numpy(A.astype(np.float64)).cuda(), torch.from_numpy(B.astype(np.float64)).cuda(),
+                    want, kw))
+    torch.cuda.synchronize()
+    return out
+
+
+def rounds(problems, streams, count, first, bad):
+    outs = []
+    for r in range(count):
+        p, A, B, want, kw = problems[(first + r) % len(problems)]
+        s = streams[r % len(streams)]
+        C = torch.empty_like(want)
+        mmp.mm_modp_async(A, B, C, p, stream=s, **kw)
+        outs.append((C, want))
+    for s in streams:
+        s.synchronize()
+    bad.extend(i for i, (C, want) in enumerate(outs) if not torch.equal(C, want))
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("nstreams", [1, 3])
+def test_streams_share_kept_workspaces(problems, nstreams):
+    bad = []
+    streams = [torch.cuda.Stream() for _ in range(nstreams)]
+    say("streams", nstreams)
+    rounds(problems, streams, 60, 0, bad)
+    assert not bad
+
+
+def test_threads_share_kept_workspaces(problems):
+    bad = []
+    threads = [threading.Thread(target=rounds, args=(problems, [torch.cuda.Stream(), torch.cuda.Stream()], 30, t, bad))
+               for t in range(4)]
+    say("threads", len(threads))
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
