@@ -34,9 +34,16 @@ struct Planned {
   const mmp_job* job;
   mmp_plan_t plan;
   size_t ws_offset;
+  bool residues;  // in the residue form
+  RnsPlan rns;
 };
 
-int plan_batch(const mmp_job* jobs, int count, const mmp_opts* opts, std::vector<Planned>* out,
+// together: AUTO products of a batch of two or more are planned for the launches
+// they share.  One on FP64 words would be a launch of its own with the chip mostly
+// idle (40 to 170 us each in a batch of 32 with sizes 64 to 4096); on INT8 words
+// it fills in beside the others.  And each takes the residue form where that is
+// less of the chip's time.
+int plan_batch(const mmp_job* jobs, int count, const mmp_opts* opts, bool together, std::vector<Planned>* out,
                size_t* ws_total) {
   if (count < 0 || (count > 0 && !jobs)) return MMP_EINVAL;
   // batched products run one k-range each (their many tiles fill the chip)
@@ -45,9 +52,11 @@ int plan_batch(const mmp_job* jobs, int count, const mmp_opts* opts, std::vector
   if (opts) o1 = *opts;
   o1.splits = 1;
   opts = &o1;
+  together = together && count >= 2 && o1.form == MMP_FORM_AUTO && o1.batch_launch == 0 && !o1.tile &&
+             !o1.force_kblock && !o1.extended_block && !o1.centered_words;
   out->clear();
   out->reserve(count);
-  size_t ws = 0;
+  double digits_us = 0.0;
   for (int i = 0; i < count; i++) {
     const mmp_job& j = jobs[i];
     if (int st = check_product_args(j.m, j.n, j.k, j.A, j.lda, j.B, j.ldb, j.C, j.ldc)) return st;
@@ -55,10 +64,37 @@ int plan_batch(const mmp_job* jobs, int count, const mmp_opts* opts, std::vector
     pj.job = &j;
     if (int st = mmp::plan(j.p, j.u, j.v, j.m, j.n, j.k, opts, &pj.plan)) return st;
     if (!fp64_ld_ok(pj.plan, j.lda, j.ldb)) return MMP_EINVAL;
+    pj.residues = false;
+    const bool empty = j.m == 0 || j.n == 0 || j.k == 0;
+    if (together && j.u == 0 && !empty) {
+      TunedChoice tuned;  // a measured choice stands
+      if (pj.plan.form == MMP_FORM_FP64_WORDS && !tune_lookup(j.p, j.m, j.n, j.k, 0, &tuned)) {
+        mmp_opts o2 = o1;
+        o2.form = MMP_FORM_INT8_WORDS;
+        if (int st = mmp::plan(j.p, 0, 0, j.m, j.n, j.k, &o2, &pj.plan)) return st;
+      }
+      if (pj.plan.form == MMP_FORM_INT8_WORDS) {
+        double us;
+        pj.residues = rns_batch_chosen(j.p, j.m, j.n, j.k, &pj.rns, &us);
+        digits_us += us;
+      }
+    }
+    out->push_back(pj);
+  }
+  // Small batches stay whole on their digits, two launches instead of five (16
+  // products with sizes 64 to 1000, 75 us of kernels: 87 us against 95).  Residue
+  // planes up to kMaxResidueBytes in all; further products on their digits.
+  constexpr size_t kMaxResidueBytes = (size_t)8 << 30;
+  constexpr double kSmallBatchUs = 120.0;
+  size_t ws = 0, residue_bytes = 0;
+  for (Planned& pj : *out) {
+    const mmp_job& j = *pj.job;
+    if (pj.residues && (digits_us < kSmallBatchUs || residue_bytes + pj.rns.bytes > kMaxResidueBytes))
+      pj.residues = false;
+    if (pj.residues) residue_bytes += pj.rns.bytes;
     pj.ws_offset = ws;
     if (pj.plan.form == MMP_FORM_INT8_WORDS && j.m > 0 && j.n > 0 && j.k > 0)
-      ws += align_up(pj.plan.workspace_bytes);
-    out->push_back(pj);
+      ws += align_up(pj.residues ? pj.rns.bytes : pj.plan.workspace_bytes);
   }
   // outputs must not overlap each other
   for (int a = 0; a < count; a++)
@@ -117,14 +153,22 @@ int run_batch(const std::vector<Planned>& pj, const mmp_opts* opts, size_t ws_to
   const int mode = opts ? opts->batch_launch : 0;
   std::vector<Int8Args> all;
   std::vector<int> all_digits;
+  std::vector<RnsBatchJob> residues;
   for (const Planned& x : pj) {
     const mmp_job& j = *x.job;
     if (j.m == 0 || j.n == 0 || j.k == 0 || x.plan.form != MMP_FORM_INT8_WORDS) continue;
-    all.push_back(make_int8_args(x.plan, j.m, j.n, j.k, j.A, j.lda, j.B, j.ldb, j.C, j.ldc,
-                                 (int8_t*)work + x.ws_offset));
+    const Int8Args g = make_int8_args(x.plan, j.m, j.n, j.k, j.A, j.lda, j.B, j.ldb, j.C, j.ldc,
+                                      (int8_t*)work + x.ws_offset);
+    if (x.residues) {
+      residues.push_back({g, x.rns});
+      continue;
+    }
+    all.push_back(g);
     all_digits.push_back(x.plan.digits_a);
   }
-  if (mode == 2 || (mode == 0 && all.size() >= 2)) {
+  for (size_t c = 0; c < residues.size() && !err; c += kMaxRnsBatch)
+    err = launch_rns_batch(residues.data() + c, (int)std::min<size_t>(kMaxRnsBatch, residues.size() - c), stream);
+  if (mode == 2 || (mode == 0 && (all.size() >= 2 || !residues.empty()))) {
     for (size_t c = 0; c < all.size() && !err; c += kMaxMixedBatch) {
       const int nj = (int)std::min<size_t>(kMaxMixedBatch, all.size() - c);
       err = launch_int8_batch(all.data() + c, all_digits.data() + c, nj, stream);
@@ -178,7 +222,7 @@ extern "C" {
 size_t mmp_workspace_batched(const mmp_job* jobs, int count, const mmp_opts* opts) {
   std::vector<Planned> pj;
   size_t ws = 0;
-  if (plan_batch(jobs, count, opts, &pj, &ws) != MMP_OK) return 0;
+  if (plan_batch(jobs, count, opts, true, &pj, &ws) != MMP_OK) return 0;
   return ws;
 }
 
@@ -186,7 +230,15 @@ int mm_modp_batched(const mmp_job* jobs, int count, const mmp_opts* opts, void* 
   try {
     std::vector<Planned> pj;
     size_t ws = 0;
-    if (int st = plan_batch(jobs, count, opts, &pj, &ws)) return st;
+    if (int st = plan_batch(jobs, count, opts, true, &pj, &ws)) return st;
+    // a caller's workspace too small for that (or unaligned): each product as planned on its own
+    if (opts && opts->workspace && (opts->workspace_bytes < ws || (uintptr_t)opts->workspace % 16))
+      if (int st = plan_batch(jobs, count, opts, false, &pj, &ws)) return st;
+    const int st = run_batch(pj, opts, ws, stream);
+    if (st != MMP_ENOMEM || (opts && opts->workspace)) return st;
+    // no memory for the shared launches' planes: again with each product's own
+    (void)hipGetLastError();
+    if (int st2 = plan_batch(jobs, count, opts, false, &pj, &ws)) return st2;
     return run_batch(pj, opts, ws, stream);
   } catch (...) {
     return MMP_EINVAL;

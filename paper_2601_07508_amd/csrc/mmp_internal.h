@@ -207,6 +207,16 @@ int rns_moduli(double log2_bound);  // moduli for integers up to 2^log2_bound in
 // estimated faster in the residue form than on its digit planes.
 bool rns_chosen(uint64_t p, int64_t m, int64_t n, int64_t k, const mmp_opts* opts, RnsPlan* r);
 int launch_rns(const RnsPlan& r, const Int8Args& g, void* stream);
+// Products of a batch: true when this one belongs in the residue form's shared
+// launches rather than the digits', with *r for launch_rns_batch (each product's
+// workspace at g.work).  *digits_us: its estimated time on its digits.
+struct RnsBatchJob {
+  Int8Args g;
+  RnsPlan plan;
+};
+constexpr int kMaxRnsBatch = 64;
+bool rns_batch_chosen(uint64_t p, int64_t m, int64_t n, int64_t k, RnsPlan* r, double* digits_us);
+int launch_rns_batch(const RnsBatchJob* jobs, int njobs, void* stream);
 // The multi-modular product in the same form: X in `limbs` limbs of base
 // 2^base_bits, which every prime reduces.
 struct RnsCrt {

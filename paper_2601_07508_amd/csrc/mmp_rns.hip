@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstring>
 #include <type_traits>
+#include <vector>
 
 #include "rns_kernel.h"
 
@@ -129,45 +130,80 @@ int launch_convert(const RnsPlan& r, const In& A, int64_t m, int64_t lda, const 
   return e;
 }
 
-// The INT8 products, and where their residues lie.
+// One product's entry of the GEMM's table (its items from `start` on; returns
+// how many), and where its residues lie.
 template <class S>
-int launch_products(const RnsPlan& r, int64_t m, int64_t n, int64_t k, int8_t* planes, hipStream_t s, rns::RnsOut* o) {
+int64_t gemm_job(const RnsPlan& r, int64_t m, int64_t n, int64_t k, int8_t* planes, int64_t start, rns::GemmJob* g,
+                 rns::RnsOut* o) {
   using namespace rns;
-  RnsGemmArgs a;
-  std::memset(&a, 0, sizeof(a));
-  a.Ad = planes;
-  a.Bd = planes + r.bytes_a;
-  a.res = planes + r.bytes_a + r.bytes_b;
-  a.kp = cdiv(k, 64) * 64;
-  a.ablk = (int)row_blocks(m);
-  a.bblk = (int)row_blocks(n);
-  a.tiles_m = (int)cdiv(m, S::BM);
-  a.tiles_n = (int)cdiv(n, S::BN);
-  a.n = r.n;
-  a.splits = r.splits;
-  a.stages = (int)(a.kp / 64);
-  a.per_split = (int)cdiv(a.stages, r.splits);
+  g->Ad = planes;
+  g->Bd = planes + r.bytes_a;
+  g->res = planes + r.bytes_a + r.bytes_b;
+  g->kp = cdiv(k, 64) * 64;
+  g->ablk = (int)row_blocks(m);
+  g->bblk = (int)row_blocks(n);
+  g->tiles_m = (int)cdiv(m, S::BM);
+  g->tiles_n = (int)cdiv(n, S::BN);
+  g->n = r.n;
+  g->splits = r.splits;
+  g->stages = (int)(g->kp / 64);
+  g->per_split = (int)cdiv(g->stages, r.splits);
+  g->start = (int)start;
+  o->res = g->res;
+  o->m = m;
+  o->n = n;
+  o->tiles_m = g->tiles_m;
+  o->tiles_n = g->tiles_n;
+  o->nmod = r.n;
+  o->splits = r.splits;
+  return (int64_t)g->tiles_m * g->tiles_n * r.n * r.splits;
+}
+
+template <class S, int JOBS>
+int launch_gemm(rns::RnsGemmArgs<JOBS>& a, hipStream_t s) {
   std::memcpy(a.c, tables().gemm, sizeof(a.c));
-  const int64_t items = (int64_t)a.tiles_m * a.tiles_n * r.n * r.splits;
-  const int64_t grid = std::min<int64_t>(items, (int64_t)current_cus() * S::GROUPS);
-  TimerTok* t = timer_begin("rns_gemm");
-  hipExtLaunchKernelGGL((rns_gemm_kernel<S>), dim3((unsigned)grid), dim3(S::THREADS), 0, s, timer_start(t),
+  const int64_t grid = std::min<int64_t>(a.total, (int64_t)current_cus() * S::GROUPS);
+  TimerTok* t = timer_begin(JOBS == 1 ? "rns_gemm" : "rns_batch_gemm");
+  hipExtLaunchKernelGGL((rns::rns_gemm_kernel<S, JOBS>), dim3((unsigned)grid), dim3(S::THREADS), 0, s, timer_start(t),
                         timer_stop(t), 0, a);
   const int e = (int)hipGetLastError();
   timer_commit(t, e);
-  o->res = a.res;
-  o->m = m;
-  o->n = n;
-  o->tiles_m = a.tiles_m;
-  o->tiles_n = a.tiles_n;
-  o->nmod = r.n;
-  o->splits = r.splits;
   return e;
+}
+
+// The INT8 products of one product.
+template <class S>
+int launch_products(const RnsPlan& r, int64_t m, int64_t n, int64_t k, int8_t* planes, hipStream_t s, rns::RnsOut* o) {
+  rns::RnsGemmArgs<1> a;
+  std::memset(&a, 0, sizeof(a));
+  a.njobs = 1;
+  a.total = (int)gemm_job<S>(r, m, n, k, planes, 0, &a.job[0], o);
+  return launch_gemm<S, 1>(a, s);
 }
 
 template <class S>
 int64_t units_of(const rns::RnsOut& o) {
   return (int64_t)o.tiles_m * o.tiles_n * S::NW * S::XB * S::YB / 4;
+}
+
+// The recombination's constants mod p.
+void combine_args(const RnsPlan& r, const Int8Args& g, rns::CombineArgs* b) {
+  b->o.ldc = g.ldc;
+  b->C = g.C;
+  b->p = (double)g.p;
+  b->q = g.q;
+  // M / m_t mod p as the product of the moduli before t and those after it
+  uint64_t after[kRnsMaxModuli + 1], before = 1;
+  after[r.n] = 1;
+  for (int i = r.n - 1; i >= 0; i--) after[i] = mulmod_u64(after[i + 1], (uint64_t)kModuli[i], g.p);
+  split26(after[0] % g.p, g.p, &b->mhi, &b->mlo);
+  for (int i = 0; i < r.n; i++) {
+    const int inv = tables().inv[r.n][i];
+    const uint64_t iv = (uint64_t)(inv < 0 ? inv + (int64_t)g.p : inv);  // p >= 2^16
+    split26(mulmod_u64(mulmod_u64(before, after[i + 1], g.p), iv, g.p), g.p, &b->whi[i], &b->wlo[i]);
+    b->f[i] = (double)inv / (double)kModuli[i];
+    before = mulmod_u64(before, (uint64_t)kModuli[i], g.p);
+  }
 }
 
 template <class S>
@@ -176,28 +212,54 @@ int launch_mod_p(const RnsPlan& r, const Int8Args& g, int8_t* planes, hipStream_
   CombineArgs b;
   std::memset(&b, 0, sizeof(b));
   if (int e = launch_products<S>(r, g.m, g.n, g.k, planes, s, &b.o)) return e;
-  b.o.ldc = g.ldc;
-  b.C = g.C;
-  b.p = (double)g.p;
-  b.q = g.q;
-  // M / m_t mod p as the product of the moduli before t and those after it
-  uint64_t after[kRnsMaxModuli + 1], before = 1;
-  after[r.n] = 1;
-  for (int i = r.n - 1; i >= 0; i--) after[i] = mulmod_u64(after[i + 1], (uint64_t)kModuli[i], g.p);
-  split26(after[0] % g.p, g.p, &b.mhi, &b.mlo);
-  for (int i = 0; i < r.n; i++) {
-    const int inv = tables().inv[r.n][i];
-    const uint64_t iv = (uint64_t)(inv < 0 ? inv + (int64_t)g.p : inv);  // p >= 2^16
-    split26(mulmod_u64(mulmod_u64(before, after[i + 1], g.p), iv, g.p), g.p, &b.whi[i], &b.wlo[i]);
-    b.f[i] = (double)inv / (double)kModuli[i];
-    before = mulmod_u64(before, (uint64_t)kModuli[i], g.p);
-  }
+  combine_args(r, g, &b);
   TimerTok* t = timer_begin("rns_combine");
   hipExtLaunchKernelGGL((rns_combine_kernel<S>), dim3((unsigned)cdiv(units_of<S>(b.o), 4)), dim3(256), 0, s,
                         timer_start(t), timer_stop(t), 0, b);
   const int e = (int)hipGetLastError();
   timer_commit(t, e);
   return e;
+}
+
+// Products of one tile shape (`pick`, in table order): their INT8 products in one
+// launch, their recombinations 16 a launch.
+template <class S>
+int launch_shape_batch(const RnsBatchJob* jobs, const std::vector<int>& pick, hipStream_t s) {
+  using namespace rns;
+  if (pick.empty()) return 0;
+  RnsGemmArgs<kRnsBatch> a;
+  std::memset(&a, 0, sizeof(a));
+  std::vector<CombineArgs> outs(pick.size());
+  int64_t items = 0;
+  for (size_t i = 0; i < pick.size(); i++) {
+    const RnsBatchJob& j = jobs[pick[i]];
+    std::memset(&outs[i], 0, sizeof(outs[i]));
+    items += gemm_job<S>(j.plan, j.g.m, j.g.n, j.g.k, j.g.work, items, &a.job[i], &outs[i].o);
+    combine_args(j.plan, j.g, &outs[i]);
+  }
+  if (items > 0x3fffffff) return (int)hipErrorInvalidValue;
+  a.njobs = (int)pick.size();
+  a.total = (int)items;
+  if (int e = launch_gemm<S, kRnsBatch>(a, s)) return e;
+  for (size_t c = 0; c < outs.size(); c += kCombineBatch) {
+    CombineBatch b;
+    std::memset(&b, 0, sizeof(b));
+    b.njobs = (int)std::min<size_t>(kCombineBatch, outs.size() - c);
+    int64_t groups = 0;
+    for (int i = 0; i < b.njobs; i++) {
+      b.start[i] = (int)groups;
+      b.job[i] = outs[c + i];
+      groups += cdiv(units_of<S>(outs[c + i].o), 4);
+    }
+    if (groups > 0x7fffffff) return (int)hipErrorInvalidValue;
+    TimerTok* t = timer_begin("rns_batch_combine");
+    hipExtLaunchKernelGGL((rns_combine_batch_kernel<S>), dim3((unsigned)groups), dim3(256), 0, s, timer_start(t),
+                          timer_stop(t), 0, b);
+    const int e = (int)hipGetLastError();
+    timer_commit(t, e);
+    if (e) return e;
+  }
+  return 0;
 }
 
 // Integers of up to 192 bits, two's complement, as 32-bit words: W_t and M.
@@ -342,14 +404,15 @@ double residues_us(const RnsPlan& r, int64_t m, int64_t n, int64_t k, int64_t it
 
 // One tile shape's plan for nm moduli; false beyond the kernels' index ranges.
 template <class S>
-bool plan_shape(int nm, int64_t m, int64_t n, int64_t k, RnsPlan* r) {
+bool plan_shape(int nm, int64_t m, int64_t n, int64_t k, RnsPlan* r, bool alone = true) {
   using namespace rns;
   const int64_t stages = cdiv(k, 64), kp = stages * 64, tiles = cdiv(m, S::BM) * cdiv(n, S::BN);
   const int64_t slots = 256 * S::GROUPS;
   // k-ranges: at most 1024 stages each (the int32 bound), and while the items
   // do not fill the chip more, of at least 16 stages
-  int64_t s = cdiv(stages, 1024);
-  while (tiles * nm * s < slots && stages / (s + 1) >= 16 && s < 64) s++;
+  // (in a batch, others do): of at most 128, or the last would run on alone
+  int64_t s = cdiv(stages, alone ? 1024 : 128);
+  while (alone && tiles * nm * s < slots && stages / (s + 1) >= 16 && s < 64) s++;
   if (s > 64) return false;
   const int64_t per = cdiv(stages, s);
   r->n = nm;
@@ -402,6 +465,83 @@ int launch_rns(const RnsPlan& r, const Int8Args& g, void* stream) {
                           : launch_convert<CenteredIn, false>(r, A, g.m, g.lda, B, g.n, g.ldb, g.k, g.work, s);
   if (e) return e;
   return r.large ? launch_mod_p<RnsLarge>(r, g, g.work, s) : launch_mod_p<RnsSmall>(r, g, g.work, s);
+}
+
+bool rns_batch_chosen(uint64_t p, int64_t m, int64_t n, int64_t k, RnsPlan* r, double* digits_us) {
+  using namespace rns;
+  *digits_us = 0.0;
+  if (m <= 0 || n <= 0 || k <= 0 || std::max(std::max(m, n), k) > 0x7fffffff) return false;
+  // the chip's time of this product on its digits, in the launch of the whole batch
+  const int D = digits_for(p), bn = D <= 4 ? 64 : 32;
+  const double entries = ((double)m + n) * k;
+  *digits_us = 0.064 / 512 * D * D * (bn / 64.0) * (double)cdiv(m, 64) * cdiv(n, bn) * cdiv(k, 64) +
+               0.233e-6 * entries * (8 + D);
+  const int nm = p < (1u << 16) ? 0 : rns_moduli(std::log2((double)k) + 2.0 * std::log2((double)(p / 2)));
+  if (nm == 0) return false;
+  RnsPlan small, large;
+  if (!plan_shape<RnsSmall>(nm, m, n, k, &small, false) || !plan_shape<RnsLarge>(nm, m, n, k, &large, false)) return false;
+  // and by its residues: a large tile's stage takes 0.65 / 256 us, a small one's 0.339 / 512
+  const double st = (double)cdiv(k, 64) * nm;
+  const double tl = 0.65 / 256 * st * (double)cdiv(m, RnsLarge::BM) * cdiv(n, RnsLarge::BN);
+  const double ts = 0.339 / 512 * st * (double)cdiv(m, RnsSmall::BM) * cdiv(n, RnsSmall::BN);
+  *r = tl < ts ? large : small;
+  const double residues = std::min(tl, ts) + 0.233e-6 * entries * (8 + nm) + 0.22e-6 * (double)m * n * (2 * nm + 8);
+  // The digits' launch holds the code of every digit count, at 64 x 32 tiles from
+  // five digits on, and runs well below that estimate: batches of 32 and 64
+  // products with sizes 64 to 4096 took 1553 and 1112 us with every product on its
+  // digits, 1154 and 953 with those whose residues take less than 1.3 times the
+  // estimate, 1112 and 924 with 3 times, 1106 and 937 with all.
+  return residues < 3.0 * *digits_us;
+}
+
+int launch_rns_batch(const RnsBatchJob* jobs, int njobs, void* stream) {
+  using namespace rns;
+  if (njobs < 1 || njobs > kRnsBatch) return (int)hipErrorInvalidValue;
+  hipStream_t s = (hipStream_t)stream;
+  ConvBatch b;
+  std::memset(&b, 0, sizeof(b));
+  b.ca.n = kRnsMaxModuli;
+  std::memcpy(b.ca.c, tables().conv, sizeof(b.ca.c));
+  b.njobs = njobs;
+  int64_t groups = 0;
+  std::vector<int> large, small;
+  for (int i = 0; i < njobs; i++) {
+    const Int8Args& g = jobs[i].g;
+    ConvJob& c = b.job[i];
+    c.A = g.A;
+    c.B = g.B;
+    c.p = (int64_t)g.p;
+    c.m = g.m;
+    c.n = g.n;
+    c.k = g.k;
+    c.lda = g.lda;
+    c.ldb = g.ldb;
+    c.kp = g.kp;
+    c.outA = g.work;
+    c.outB = g.work + jobs[i].plan.bytes_a;
+    c.nmod = jobs[i].plan.n;
+    c.start = (int)groups;
+    const int64_t na = row_blocks(g.m) * cdiv(g.kp, 256);
+    c.na = (int)na;
+    groups += na + cdiv(g.n, 64) * (g.kp / 64);
+    if (groups > 0x7fffffff) return (int)hipErrorInvalidValue;
+    (jobs[i].plan.large ? large : small).push_back(i);
+  }
+  TimerTok* t = timer_begin("rns_batch_convert");
+  hipExtLaunchKernelGGL(rns_convert_batch_kernel, dim3((unsigned)groups), dim3(256), 0, s, timer_start(t), timer_stop(t),
+                        0, b);
+  int e = (int)hipGetLastError();
+  timer_commit(t, e);
+  if (e) return e;
+  // longest items first, so that the short ones fill the end
+  auto longer = [&](int x, int y) {
+    const RnsPlan &a = jobs[x].plan, &c = jobs[y].plan;
+    return jobs[x].g.kp * c.splits > jobs[y].g.kp * a.splits;
+  };
+  std::stable_sort(large.begin(), large.end(), longer);
+  std::stable_sort(small.begin(), small.end(), longer);
+  e = launch_shape_batch<RnsLarge>(jobs, large, s);
+  return e ? e : launch_shape_batch<RnsSmall>(jobs, small, s);
 }
 
 // The multi-modular product of integers below 2^entry_bits: 0 <= X <

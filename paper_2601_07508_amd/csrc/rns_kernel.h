@@ -205,6 +205,58 @@ __global__ __launch_bounds__(256) void rns_convert_kernel(const ConvArgs ca, In 
   }
 }
 
+// The operands of many products in one launch.
+struct ConvJob {
+  const double *A, *B;
+  int64_t p, m, n, k, lda, ldb, kp;
+  int8_t *outA, *outB;
+  int nmod, start, na;  // first workgroup, and how many of them take A
+};
+constexpr int kRnsBatch = 64;  // products of a launch
+struct ConvBatch {
+  ConvArgs ca;  // every modulus; a product takes the first nmod
+  int njobs;
+  ConvJob job[kRnsBatch];
+};
+
+// the last product whose start is at most w (w and the starts uniform)
+template <class Jobs, class F>
+__device__ __forceinline__ int find_start(const Jobs& jobs, int njobs, int w, F start) {
+  int lo = 0, hi = njobs - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) / 2;
+    if (start(jobs[mid]) <= w)
+      lo = mid;
+    else
+      hi = mid - 1;
+  }
+  return lo;
+}
+
+template <bool WIDE>
+__device__ __forceinline__ void convert_job(const ConvBatch& b, const ConvJob& j, int64_t w, int wave, uint64_t* lds) {
+  const CenteredIn A{j.A, j.p, j.p / 2}, B{j.B, j.p, j.p / 2};
+  if (w < j.na) {
+    const int64_t per_row = (j.kp + 255) / 256, kblk = (w % per_row) * 4 + wave;
+    if (kblk * 64 < j.kp)
+      convert_rows<CenteredIn, WIDE>(A, b.ca, j.m, j.k, j.lda, j.kp, j.outA, w / per_row, kblk, 0, j.nmod, lds);
+  } else {
+    const int64_t cb = (j.n + 63) / 64;
+    convert_cols<CenteredIn, WIDE>(B, b.ca, j.k, j.n, j.ldb, j.kp, j.outB, (w - j.na) % cb, (w - j.na) / cb, wave, 0,
+                                   j.nmod);
+  }
+}
+
+__global__ __launch_bounds__(256) void rns_convert_batch_kernel(const ConvBatch b) {
+  __shared__ uint64_t lds[4][16 * kConvRow];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const ConvJob& j = b.job[find_start(b.job, b.njobs, (int)blockIdx.x, [](const ConvJob& x) { return x.start; })];
+  if (j.p >> 31)
+    convert_job<true>(b, j, (int)blockIdx.x - j.start, wave, lds[wave]);
+  else
+    convert_job<false>(b, j, (int)blockIdx.x - j.start, wave, lds[wave]);
+}
+
 // ---------------------------------------------------------------- products
 
 struct GemmConst {
@@ -214,7 +266,7 @@ struct GemmConst {
   int32_t negm;
   int32_t bias;   // accumulator start: the largest multiple of m up to 2^30
 };
-struct RnsGemmArgs {
+struct GemmJob {
   const int8_t* Ad;
   const int8_t* Bd;
   int8_t* res;
@@ -223,7 +275,14 @@ struct RnsGemmArgs {
   int tiles_m, tiles_n;
   int n, splits;
   int stages, per_split;  // 64-k stages in all, and per k-range
+  int start;              // first item
+};
+// One product, or JOBS of one tile shape whose items follow one another.
+template <int JOBS>
+struct RnsGemmArgs {
+  int njobs, total;  // total: items
   GemmConst c[kRnsMaxModuli];
+  GemmJob job[JOBS];
 };
 
 template <int N>
@@ -275,16 +334,15 @@ using RnsSmall = RnsShape<2, 2, 4, 4, 4>;
 // A persistent grid over (modulus, k-range, tile) items.  The four-stage copy
 // ring runs across items: three stages are always in flight, also through an
 // item's epilogue, so no item waits out a copy latency at its start.
-template <class S>
-__global__ __launch_bounds__(S::THREADS, S::THREADS *S::GROUPS / 256) void rns_gemm_kernel(const RnsGemmArgs a) {
+template <class S, int JOBS>
+__global__ __launch_bounds__(S::THREADS, S::THREADS *S::GROUPS / 256) void rns_gemm_kernel(const RnsGemmArgs<JOBS> a) {
   constexpr int XB = S::XB, YB = S::YB, CA = S::CA, CB = S::CB;
   constexpr int PER = S::PER;
   __shared__ __attribute__((aligned(1024))) int8_t lds[S::RING][S::STAGE];
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wv / S::WN, wn = wv % S::WN;
-  const int tiles = a.tiles_m * a.tiles_n;
-  const int total = tiles * a.n * a.splits;
+  const int total = a.total;
   const int G = (int)gridDim.x;
   // workgroups are dispatched round-robin over the 8 XCDs: give each XCD a
   // contiguous run of every round's items, so that neighbours share panels in L2
@@ -294,22 +352,26 @@ __global__ __launch_bounds__(S::THREADS, S::THREADS *S::GROUPS / 256) void rns_g
     first = (xcd < rem) ? xcd * (per + 1) + loc : rem * (per + 1) + (xcd - rem) * per + loc;
   }
   struct Item {
-    int t, s, tile, tm, tn, st0, nst;
+    int j, t, s, tile, tm, tn, st0, nst;
   };
   auto div = [](int x, int y) { return __builtin_amdgcn_readfirstlane(x / y); };  // both uniform
   auto item_of = [&](int it) {
     Item x;
-    const int ts = div(it, tiles);
-    x.tile = it - ts * tiles;
-    x.t = div(ts, a.splits);
-    x.s = ts - x.t * a.splits;
+    x.j = JOBS == 1 ? 0 : __builtin_amdgcn_readfirstlane(
+                              find_start(a.job, a.njobs, it, [](const GemmJob& g) { return g.start; }));
+    const GemmJob& g = a.job[x.j];
+    const int tiles = g.tiles_m * g.tiles_n, local = it - g.start;
+    const int ts = div(local, tiles);
+    x.tile = local - ts * tiles;
+    x.t = div(ts, g.splits);
+    x.s = ts - x.t * g.splits;
     // groups of 8 tile rows, column by column
-    const int group = 8 * a.tiles_n, gid = div(x.tile, group), f = gid * 8;
-    const int gm = min(a.tiles_m - f, 8), in = x.tile - gid * group;
+    const int group = 8 * g.tiles_n, gid = div(x.tile, group), f = gid * 8;
+    const int gm = min(g.tiles_m - f, 8), in = x.tile - gid * group;
     x.tn = div(in, gm);
     x.tm = f + in - x.tn * gm;
-    x.st0 = x.s * a.per_split;
-    x.nst = min(a.per_split, a.stages - x.st0);
+    x.st0 = x.s * g.per_split;
+    x.nst = min(g.per_split, g.stages - x.st0);
     return x;
   };
 
@@ -318,21 +380,22 @@ __global__ __launch_bounds__(S::THREADS, S::THREADS *S::GROUPS / 256) void rns_g
   // global_load_lds the compiler drains every outstanding LDS read at each
   // wait for one (it takes the copy for a flat access to LDS), which undid the
   // read-ahead below.
-  const int64_t rowA = a.kp * 16, planeA = (int64_t)a.ablk * rowA, planeB = (int64_t)a.bblk * rowA;
   __amdgpu_buffer_rsrc_t ra, rb;
   uint32_t off[CA + CB];
   int c_item = first, c_left = 0;
   auto aim = [&](int it) {
     const Item x = item_of(it);
+    const GemmJob& g = a.job[x.j];
+    const int64_t row = g.kp * 16, planeA = (int64_t)g.ablk * row, planeB = (int64_t)g.bblk * row;
     c_left = x.nst;
-    ra = __builtin_amdgcn_make_buffer_rsrc((void*)(a.Ad + x.t * planeA), (short)0, (int)(uint32_t)planeA, kBufferWord3);
-    rb = __builtin_amdgcn_make_buffer_rsrc((void*)(a.Bd + x.t * planeB), (short)0, (int)(uint32_t)planeB, kBufferWord3);
+    ra = __builtin_amdgcn_make_buffer_rsrc((void*)(g.Ad + x.t * planeA), (short)0, (int)(uint32_t)planeA, kBufferWord3);
+    rb = __builtin_amdgcn_make_buffer_rsrc((void*)(g.Bd + x.t * planeB), (short)0, (int)(uint32_t)planeB, kBufferWord3);
 #pragma unroll
     for (int e = 0; e < CA; e++)
-      off[e] = (uint32_t)(min(x.tm * S::MB + wv * CA + e, a.ablk - 1) * rowA) + (uint32_t)x.st0 * 1024u;
+      off[e] = (uint32_t)(min(x.tm * S::MB + wv * CA + e, g.ablk - 1) * row) + (uint32_t)x.st0 * 1024u;
 #pragma unroll
     for (int e = 0; e < CB; e++)
-      off[CA + e] = (uint32_t)(min(x.tn * S::NB + wv * CB + e, a.bblk - 1) * rowA) + (uint32_t)x.st0 * 1024u;
+      off[CA + e] = (uint32_t)(min(x.tn * S::NB + wv * CB + e, g.bblk - 1) * row) + (uint32_t)x.st0 * 1024u;
   };
   // the cursor's stage, one step on: called once before each stage's copies
   auto advance = [&]() {
@@ -453,7 +516,8 @@ __global__ __launch_bounds__(S::THREADS, S::THREADS *S::GROUPS / 256) void rns_g
     // within 2^30 of zero and the biased accumulator in [0, 2^31]:
     // y = hi (2^16 mod m) + lo <= 2^15 225 + 2^16 < 2^23 - 2^16 is congruent to
     // it, and is reduced as in the conversion, from O just above 2^23.
-    int8_t* dst = a.res + ((int64_t)(x.t * a.splits + x.s) * tiles + x.tile) * S::TILE_BYTES + wv * XB * YB * 256 + lane * 16;
+    const GemmJob& g = a.job[x.j];
+    int8_t* dst = g.res + ((int64_t)(x.t * g.splits + x.s) * (g.tiles_m * g.tiles_n) + x.tile) * S::TILE_BYTES + wv * XB * YB * 256 + lane * 16;
 #pragma unroll
     for (int i = 0; i < XB * YB / 4; i++) {
       int4v w;
@@ -582,11 +646,10 @@ __device__ __forceinline__ double reduce_near(double x, double p, double q) {
 // 5.1 TB/s at 8192^2 outputs and 15 moduli.
 constexpr int kOutRow = 66;
 template <class S>
-__global__ __launch_bounds__(256) void rns_combine_kernel(const CombineArgs a) {
-  __shared__ double lds[4][16 * kOutRow];
+__device__ __forceinline__ void combine_unit(const CombineArgs& a, int64_t unit, double (&lds)[4][16 * kOutRow]) {
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const Unit u = unit_of<S>(a.o, (int64_t)blockIdx.x * 4 + wv, lane);
+  const Unit u = unit_of<S>(a.o, unit + wv, lane);
   if (!u.any) return;
   double hi[16], lo[16], g[16];
 #pragma unroll
@@ -625,6 +688,26 @@ __global__ __launch_bounds__(256) void rns_combine_kernel(const CombineArgs a) {
   double* const out = a.C + row0 * a.o.ldc + col;
   if (col < a.o.n)
     for (int r = 0; r < rows; r++) __builtin_nontemporal_store(lds[wv][r * kOutRow + lane], out + r * a.o.ldc);
+}
+
+template <class S>
+__global__ __launch_bounds__(256) void rns_combine_kernel(const CombineArgs a) {
+  __shared__ double lds[4][16 * kOutRow];
+  combine_unit<S>(a, (int64_t)blockIdx.x * 4, lds);
+}
+
+// Several products of one tile shape.
+constexpr int kCombineBatch = 16;
+struct CombineBatch {
+  int njobs;
+  int start[kCombineBatch];  // first workgroup
+  CombineArgs job[kCombineBatch];
+};
+template <class S>
+__global__ __launch_bounds__(256) void rns_combine_batch_kernel(const CombineBatch b) {
+  __shared__ double lds[4][16 * kOutRow];
+  const int j = find_start(b.start, b.njobs, (int)blockIdx.x, [](int x) { return x; });
+  combine_unit<S>(b.job[j], (int64_t)((int)blockIdx.x - b.start[j]) * 4, lds);
 }
 
 // The multi-modular product's recombination: the same residues, of products of

@@ -180,3 +180,73 @@ def test_multi_modular(m, n, k, bits, small, count, pad):
         assert (got[m:] == -1.0).all() and (got[:, n:] == -1.0).all()
     if (m, k) in ((130, 520), (300, 1000), (64, 30000), (96, 70000), (100, 140000)):
         assert "rns_crt_combine" in phases, phases
+
+
+def batch_jobs(seed, count):
+    """Uneven products: large and small tiles, one and several k-ranges, every conversion."""
+    shapes = [(P52, 2060, 1800, 1500), (P50, 300, 200, 9000), (P31, 700, 1200, 900), (65537, 500, 260, 3000),
+              (P52, 140, 129, 2100), (251, 70, 90, 100), (P50, 64, 1000, 65)]
+    out = []
+    for i in range(count):
+        p, m, n, k = shapes[i] if i < len(shapes) else (P52, 33 + i, 65 - i // 2, 70 + i)
+        A = gen.random_matrix(seed + i, 1, m, k, p)
+        B = gen.random_matrix(seed + i, 2, k, n, p)
+        C = torch.full((m, n + 1), -1.0, dtype=torch.float64, device="cuda")[:, :n]
+        out.append((p, A, B, strided(A, i % 3, i % 2), strided(B, i % 2, 0), C))
+    return out
+
+
+def check_batch(items):
+    for p, A, B, dA, dB, C in items:
+        assert np.array_equal(C.cpu().numpy(), oracle.mm_modp(p, A, B).astype(np.float64)), (p, A.shape, B.shape)
+        assert bool((C._base[:, -1] == -1.0).all())
+
+
+def test_batch():
+    items = batch_jobs(50, 70)  # more than one launch's table
+    jobs = [(dA, dB, C, p, 0, 0) for p, A, B, dA, dB, C in items]
+    jobs[4] = jobs[4][:4] + (2, 3)  # forced binary64 words keep their own launch
+    say("residue batch")
+    phases = timed(lambda: mmp.mm_modp_batched(jobs))
+    assert phases["fp64_words"][0] == 1 and phases["rns_batch_convert"][0] >= 1, phases
+    check_batch(items)
+    # a workspace of the queried size, and one too small for the shared launches
+    need = mmp.workspace_batched(jobs)
+    own = sum(mmp.plan(j[3], *j[2].shape, j[0].shape[1], j[4], j[5], splits=1)["workspace_bytes"] + 256 for j in jobs)
+    assert own < need
+    for size, shared in ((need, True), (own, False)):
+        for *_, C in items:
+            C.fill_(-2.0)
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        phases = timed(lambda: mmp.mm_modp_batched(jobs, workspace=ws))
+        assert ("rns_batch_gemm" in phases) == shared, phases
+        check_batch(items)
+
+
+def test_small_batch_on_digits():
+    items = batch_jobs(150, 10)[4:]
+    jobs = [(dA, dB, C, p, 0, 0) for p, A, B, dA, dB, C in items]
+    phases = timed(lambda: mmp.mm_modp_batched(jobs))
+    assert set(phases) == {"int8_batch_digitize", "int8_batch_gemm"}, phases
+    check_batch(items)
+
+
+def test_batch_in_a_graph():
+    items = batch_jobs(250, 9)
+    jobs = [(dA, dB, C, p, 0, 0) for p, A, B, dA, dB, C in items]
+    ws = torch.empty(mmp.workspace_batched(jobs), dtype=torch.uint8, device="cuda")
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    call = lambda: mmp.mm_modp_batched(jobs, workspace=ws, stream=s)
+    assert "rns_batch_gemm" in timed(call)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        call()
+    for rep in range(3):
+        for *_, C in items:
+            C.fill_(-2.0)
+        ws.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        check_batch(items)
