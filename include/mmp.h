@@ -221,7 +221,11 @@ int mm_modp(uint64_t p, int u, int v, int64_t m, int64_t n, int64_t k,
    doubles must stay below 2^28.  Beyond that an AUTO call (u = v = 0, no
    word-form option) takes the INT8-digit form, and a call that forces the
    FP64 form returns MMP_EINVAL before any device work.  Batched products
-   return MMP_EINVAL; the server plans such a request in the INT8 form. */
+   return MMP_EINVAL; the server plans such a request in the INT8 form.
+   An AUTO call that mmp_plan gives to FP64 words runs on INT8 words where
+   those are estimated faster from measured times and their memory is there
+   (a caller's workspace that holds it, or the library's own outside a
+   capture); the result is the same. */
 int mm_modp_async(const mmp_opts *opts, uint64_t p, int u, int v, int64_t m,
                   int64_t n, int64_t k, const double *A, int64_t lda,
                   const double *B, int64_t ldb, double *C, int64_t ldc,

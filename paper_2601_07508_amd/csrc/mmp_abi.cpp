@@ -408,6 +408,69 @@ int run_planned(const mmp_plan_t& pl, const mmp_opts* opts, int64_t m, int64_t n
   return st ? st : st2;
 }
 
+// Whether a product planned on FP64 words may take p8's workspace instead: the
+// caller's where it holds it, else the library's, within the limit that the residue
+// form keeps to.  A capture without a workspace records no allocation that the
+// plan does not call for.
+static bool int8_memory(const mmp_plan_t& p8, const mmp_opts* opts, void* stream) {
+  if (opts && opts->workspace)
+    return opts->workspace_bytes >= p8.workspace_bytes && (uintptr_t)opts->workspace % 16 == 0;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing((hipStream_t)stream, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return cap == hipStreamCaptureStatusNone && p8.workspace_bytes <= kInt8MaxBytes;
+}
+
+int product_async(const mmp_opts* opts, uint64_t p, int u, int v, int64_t m, int64_t n, int64_t k,
+                  const double* A, int64_t lda, const double* B, int64_t ldb, double* C, int64_t ldc,
+                  void* stream, bool faster) {
+  try {
+    if (int st = check_product_args(m, n, k, A, lda, B, ldb, C, ldc)) return st;
+    if (opts && opts->batch_launch) return MMP_EINVAL;  // a batch option
+    const mmp_operand_t* pa = opts ? opts->prepared_a : nullptr;
+    const mmp_operand_t* pb = opts ? opts->prepared_b : nullptr;
+    mmp_plan_t pl;
+    if (pa || pb) {
+      // prepared digit planes: the INT8 form, planned without them
+      if (u != 0 || opts->form == MMP_FORM_FP64_WORDS || opts->tile || opts->extended_block ||
+          opts->centered_words)
+        return MMP_EINVAL;
+      mmp_opts o2 = *opts;
+      o2.form = MMP_FORM_INT8_WORDS;
+      o2.prepared_a = nullptr;
+      o2.prepared_b = nullptr;
+      if (int st = mmp::plan(p, 0, 0, m, n, k, &o2, &pl)) return st;
+      if (pa && !operand_fits(*pa, 0, p, m, k, pl.digits_a)) return MMP_EINVAL;
+      if (pb && !operand_fits(*pb, 1, p, k, n, pl.digits_b)) return MMP_EINVAL;
+    } else if (int st = mmp::plan(p, u, v, m, n, k, opts, &pl)) {
+      return st;
+    }
+    if (!fp64_ld_ok(pl, lda, ldb)) {
+      // leading dimensions beyond the FP64 kernel's offsets: an AUTO plan
+      // takes the INT8 form, which has no such limit; a forced one fails
+      if (u != 0 || (opts && (opts->form != MMP_FORM_AUTO || opts->tile || opts->force_kblock ||
+                              opts->extended_block || opts->centered_words)))
+        return MMP_EINVAL;
+      mmp_opts o2;
+      std::memset(&o2, 0, sizeof(o2));
+      if (opts) o2 = *opts;
+      o2.form = MMP_FORM_INT8_WORDS;
+      if (int st = mmp::plan(p, 0, 0, m, n, k, &o2, &pl)) return st;
+    }
+    mmp_plan_t p8;
+    if (faster && u == 0 && !pa && !pb && int8_instead(pl, m, n, k, opts, &p8) && int8_memory(p8, opts, stream)) {
+      const int st = run_planned(p8, opts, m, n, k, A, lda, B, ldb, C, ldc, stream);
+      if (st != MMP_ENOMEM) return st;
+      (void)hipGetLastError();
+    }
+    return run_planned(pl, opts, m, n, k, A, lda, B, ldb, C, ldc, stream);
+  } catch (...) {
+    return MMP_EINVAL;
+  }
+}
+
 }  // namespace mmp
 
 using namespace mmp;
@@ -492,43 +555,7 @@ size_t mmp_footprint(const mmp_job* job, const mmp_plan_t* plan) {
 int mm_modp_async(const mmp_opts* opts, uint64_t p, int u, int v, int64_t m, int64_t n, int64_t k,
                   const double* A, int64_t lda, const double* B, int64_t ldb, double* C, int64_t ldc,
                   void* stream) {
-  try {
-    if (int st = check_product_args(m, n, k, A, lda, B, ldb, C, ldc)) return st;
-    if (opts && opts->batch_launch) return MMP_EINVAL;  // a batch option
-    const mmp_operand_t* pa = opts ? opts->prepared_a : nullptr;
-    const mmp_operand_t* pb = opts ? opts->prepared_b : nullptr;
-    mmp_plan_t pl;
-    if (pa || pb) {
-      // prepared digit planes: the INT8 form, planned without them
-      if (u != 0 || opts->form == MMP_FORM_FP64_WORDS || opts->tile || opts->extended_block ||
-          opts->centered_words)
-        return MMP_EINVAL;
-      mmp_opts o2 = *opts;
-      o2.form = MMP_FORM_INT8_WORDS;
-      o2.prepared_a = nullptr;
-      o2.prepared_b = nullptr;
-      if (int st = mmp::plan(p, 0, 0, m, n, k, &o2, &pl)) return st;
-      if (pa && !operand_fits(*pa, 0, p, m, k, pl.digits_a)) return MMP_EINVAL;
-      if (pb && !operand_fits(*pb, 1, p, k, n, pl.digits_b)) return MMP_EINVAL;
-    } else if (int st = mmp::plan(p, u, v, m, n, k, opts, &pl)) {
-      return st;
-    }
-    if (!fp64_ld_ok(pl, lda, ldb)) {
-      // leading dimensions beyond the FP64 kernel's offsets: an AUTO plan
-      // takes the INT8 form, which has no such limit; a forced one fails
-      if (u != 0 || (opts && (opts->form != MMP_FORM_AUTO || opts->tile || opts->force_kblock ||
-                              opts->extended_block || opts->centered_words)))
-        return MMP_EINVAL;
-      mmp_opts o2;
-      std::memset(&o2, 0, sizeof(o2));
-      if (opts) o2 = *opts;
-      o2.form = MMP_FORM_INT8_WORDS;
-      if (int st = mmp::plan(p, 0, 0, m, n, k, &o2, &pl)) return st;
-    }
-    return run_planned(pl, opts, m, n, k, A, lda, B, ldb, C, ldc, stream);
-  } catch (...) {
-    return MMP_EINVAL;
-  }
+  return product_async(opts, p, u, v, m, n, k, A, lda, B, ldb, C, ldc, stream, true);
 }
 
 size_t mmp_operand_bytes(uint64_t p, int side, int64_t rows, int64_t cols) {

@@ -192,10 +192,18 @@ int launch_int8_gemm(int digits, const Int8Args* jobs, int njobs, void* stream);
 constexpr int kMaxMixedBatch = 64;
 int launch_int8_batch(const Int8Args* jobs, const int* digits, int njobs, void* stream);
 
+// True (and an INT8 plan in *out) when an AUTO call planned on FP64 words with
+// these options is estimated faster on INT8 words, by measured times rather than
+// the plan's peak rates.
+bool int8_instead(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t k, const mmp_opts* opts, mmp_plan_t* out);
 // Residue form of an INT8 product (rns_kernel.h): n moduli of at most 256,
 // `splits` k-ranges, and a workspace of A's planes, B's planes and the
 // outputs' residue bytes.
 constexpr int kRnsMaxModuli = 20;
+// Device memory that a product may take in this form (beyond it the digits'
+// planes, two to three times smaller, are used), or for INT8 words that its plan
+// does not call for.
+constexpr size_t kInt8MaxBytes = (size_t)16 << 30;
 struct RnsPlan {
   int n, splits;
   bool large;  // 256 x 256 tiles, else 128 x 128
@@ -206,6 +214,9 @@ int rns_moduli(double log2_bound);  // moduli for integers up to 2^log2_bound in
 // True (and *r) when an AUTO call's INT8 product of these sizes and options is
 // estimated faster in the residue form than on its digit planes.
 bool rns_chosen(uint64_t p, int64_t m, int64_t n, int64_t k, const mmp_opts* opts, RnsPlan* r);
+// Estimated microseconds of an AUTO call's INT8 product in the form it takes, and
+// the residue form's workspace (0 on digits).
+double int8_us(uint64_t p, int64_t m, int64_t n, int64_t k, const mmp_opts* opts, size_t* residue_bytes);
 int launch_rns(const RnsPlan& r, const Int8Args& g, void* stream);
 // Products of a batch: true when this one belongs in the residue form's shared
 // launches rather than the digits', with *r for launch_rns_batch (each product's
@@ -296,6 +307,10 @@ Int8Args make_int8_args(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t k, c
 // where rns_chosen says so.
 int run_planned(const mmp_plan_t& pl, const mmp_opts* opts, int64_t m, int64_t n, int64_t k, const double* A,
                 int64_t lda, const double* B, int64_t ldb, double* C, int64_t ldc, void* stream);
+// mm_modp_async; with `faster` an AUTO call planned on FP64 words takes INT8 words
+// where int8_instead says so and memory for them is there.
+int product_async(const mmp_opts* opts, uint64_t p, int u, int v, int64_t m, int64_t n, int64_t k, const double* A,
+                  int64_t lda, const double* B, int64_t ldb, double* C, int64_t ldc, void* stream, bool faster);
 
 // Scan for entries outside [0, p) or non-integral; sets *flag (device int) nonzero.
 int launch_validate(const double* X, int64_t rows, int64_t cols, int64_t ld, double p, int* flag,

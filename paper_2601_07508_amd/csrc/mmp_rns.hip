@@ -432,10 +432,6 @@ bool plan_shape(int nm, int64_t m, int64_t n, int64_t k, RnsPlan* r, bool alone 
 
 }  // namespace
 
-// Device memory a product may take in this form; beyond it the digit form's
-// planes, two to three times smaller, are used.
-constexpr size_t kRnsMaxBytes = (size_t)16 << 30;
-
 bool rns_chosen(uint64_t p, int64_t m, int64_t n, int64_t k, const mmp_opts* opts, RnsPlan* r) {
   using namespace rns;
   // what asks for the digit form: MMP_FORM_INT8_WORDS by name, prepared planes, a
@@ -453,8 +449,15 @@ bool rns_chosen(uint64_t p, int64_t m, int64_t n, int64_t k, const mmp_opts* opt
   *r = small;
   RnsPlan large;
   if (plan_shape<RnsLarge>(nm, m, n, k, &large) && large.us < small.us) *r = large;
-  if (r->bytes > kRnsMaxBytes) return false;
+  if (r->bytes > kInt8MaxBytes) return false;
   return r->us < digits_us(m, n, k, digits_for(p));
+}
+
+double int8_us(uint64_t p, int64_t m, int64_t n, int64_t k, const mmp_opts* opts, size_t* bytes) {
+  RnsPlan r;
+  const bool residues = rns_chosen(p, m, n, k, opts, &r);
+  *bytes = residues ? r.bytes : 0;
+  return residues ? r.us : digits_us(m, n, k, digits_for(p));
 }
 
 int launch_rns(const RnsPlan& r, const Int8Args& g, void* stream) {
@@ -556,7 +559,7 @@ bool rns_crt_plan(int64_t m, int64_t n, int64_t k, int entry_bits, uint64_t smal
   if (!plan_shape<RnsSmall>(nm, m, n, k, &small)) return false;
   c->plan = small;
   if (plan_shape<RnsLarge>(nm, m, n, k, &large) && large.us < small.us) c->plan = large;
-  if (c->plan.bytes > kRnsMaxBytes) return false;
+  if (c->plan.bytes > kInt8MaxBytes) return false;
   // the base: 2^b (1 + 2^b / p) <= 2^50 for every prime, limbs below 2^53 before
   // their carries (20 moduli, 128, the k-ranges)
   int b = 24;

@@ -77,7 +77,7 @@ extern "C" int mm_modp_static(const mmp_opts* opts, uint64_t p, int u, int v, in
       if (int st = scratch_address(&ptr)) return st;
     o.workspace = ptr;
     o.workspace_bytes = ptr ? (size_t)MMP_STATIC_SCRATCH_BYTES : 0;
-    return mm_modp_async(&o, p, u, v, m, n, k, A, lda, B, ldb, C, ldc, stream);
+    return mmp::product_async(&o, p, u, v, m, n, k, A, lda, B, ldb, C, ldc, stream, false);
   } catch (...) {
     return MMP_EINVAL;
   }

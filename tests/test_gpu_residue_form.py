@@ -250,3 +250,52 @@ def test_batch_in_a_graph():
         g.replay()
         torch.cuda.synchronize()
         check_batch(items)
+
+
+# AUTO calls that the plan gives to FP64 words and measured times to INT8 words: a
+# short and a long k, odd strides, few digits, and (last) a small one that stays
+@pytest.mark.parametrize("p,m,n,k,pad,form", [
+    (P52, 3100, 2306, 37, 0, "int8"), (P52, 1031, 2306, 65, 1, "int8"), (137438953447, 139, 200, 1969, 0, "int8"),
+    (P50, 300, 333, 800, 3, "int8"), (P31, 700, 1025, 333, 0, "int8"), (65537, 60, 70, 150, 0, "fp64_words"),
+])
+def test_faster_words(p, m, n, k, pad, form):
+    plan = mmp.plan(p, m, n, k)
+    assert plan["form"] == mmp.FORM_FP64_WORDS
+    A = gen.random_matrix(m, 1, m, k, p)
+    B = gen.random_matrix(n, 2, k, n, p)
+    A[0, :] = B[:, 0] = p - 1
+    say("faster words", p, m, n, k, pad)
+    dA, dB = strided(A, pad, 0), strided(B, pad, 0)
+    want = oracle.mm_modp(p, A, B).astype(np.float64)
+    store = torch.full((m + 1, n + pad), -1.0, dtype=torch.float64, device="cuda")
+    C = store[:m, :n]
+
+    def run(call):
+        store.fill_(-1.0)
+        phases = timed(call)
+        got = store.cpu().numpy()
+        assert np.array_equal(got[:m, :n], want)
+        assert (got[m:] == -1.0).all() and (got[:, n:] == -1.0).all()
+        return "fp64_words" if "fp64_words" in phases else "int8"
+
+    assert run(lambda: mmp.mm_modp_async(dA, dB, C, p)) == form
+    big = torch.empty(1 << 26, dtype=torch.uint8, device="cuda")
+    assert run(lambda: mmp.mm_modp_async(dA, dB, C, p, workspace=big)) == form
+    # as planned: a workspace of the plan's size, the call without allocation, words
+    # by name, and a capture (below)
+    small = torch.empty(max(256, plan["workspace_bytes"]), dtype=torch.uint8, device="cuda")
+    assert run(lambda: mmp.mm_modp_async(dA, dB, C, p, workspace=small)) == "fp64_words"
+    assert run(lambda: mmp.mm_modp_static(dA, dB, C, p)) == "fp64_words"
+    assert run(lambda: mmp.mm_modp_async(dA, dB, C, p, form=mmp.FORM_FP64_WORDS)) == "fp64_words"
+    if plan["splits"] == 1:  # no workspace: a capture without one holds the FP64 launch alone
+        s = torch.cuda.Stream()
+        s.wait_stream(torch.cuda.current_stream())
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            mmp.mm_modp_async(dA, dB, C, p, stream=s)
+        for _ in range(3):
+            store.fill_(-1.0)
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(store.cpu().numpy()[:m, :n], want)
