@@ -48,6 +48,15 @@ inline bool fp64_wide(int slots, int64_t kblock) { return slots > 8 && !(slots <
 inline Fp64Tile fp64_tile(int tile_id, int u, int v, int slots, int64_t kblock) {
   return fp64_tile_c(tile_id, u, v, fp64_wide(slots, kblock));
 }
+// 32 x 32 tiles: whether two groups of waves share each workgroup's `stages`.  Two
+// groups where every workgroup has a CU to itself and a range long enough to share:
+// 512^3, (1,1): 14.8 us against 17.4; 48 x 241 x 1109: 25.0 against 30.7.  With more
+// workgroups CUs hold several anyway (600 x 600 x 300, (2,3): 53.7 against 44.0 with
+// one group); shorter ranges lose to the sum at the end (180 x 52 x 172, (1,3): 13.8
+// against 12.7), later where a stage has fewer MFMAs.
+inline bool fp64_two_groups(int u, int v, int bm, int bn, int64_t workgroups, int64_t stages) {
+  return bm == 32 && bn == 32 && workgroups <= 256 && stages >= (u * v >= 6 ? 8 : 16);
+}
 inline int fp64_bm(const Fp64Tile& t) { return 2 * 16 * t.tm; }
 inline int fp64_bn(const Fp64Tile& t) { return 2 * 16 * t.tn; }
 

@@ -708,12 +708,13 @@ int plan(uint64_t p, int u, int v, int64_t m, int64_t n, int64_t k, const mmp_op
 // 12000 (k to 65536) and 18 to 52 bits on one MI355X.
 static double fp64_words_us(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t k) {
   const int64_t terms = (pl.slots <= kBK && pl.kblock < pl.slots) ? (kBK / pl.slots) * pl.kblock : kBK;
-  const double chain = (double)cdiv(cdiv(k, terms), pl.splits);
+  const int64_t stages = cdiv(k, terms), range = cdiv(stages, pl.splits);
   const int64_t tm = cdiv(m, pl.bm), tn = cdiv(n, pl.bn), items = tm * tn * pl.splits;
+  const bool shared = fp64_two_groups(pl.u, pl.v, pl.bm, pl.bn, items, stages / pl.splits);
   const double work = (double)pl.u * pl.v * (pl.bm / 32) * (pl.bn / 32);
-  return 7.1 + chain * (0.121 + 0.127 * (pl.u + pl.v)) + 0.079 * (double)cdiv(items, 512) * chain * work +
-         (double)items / 512 * work * (0.199 * chain + 0.658) +
-         0.157e-6 * ((double)tn * m * k + (double)tm * k * n) + (pl.splits > 1 ? 12.4 : 0.0);
+  return 6.9 + 0.095 * (double)cdiv(range, shared ? 2 : 1) * (pl.u + pl.v) +
+         0.101 * (double)(cdiv(items, 512) * range) * work + (double)items / 512 * work * (0.168 * (double)range + 0.62) +
+         0.170e-6 * ((double)tn * m * k + (double)tm * k * n) + (pl.splits > 1 ? 7.5 : 0.0);
 }
 
 bool int8_instead(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t k, const mmp_opts* opts, mmp_plan_t* out) {
@@ -724,15 +725,14 @@ bool int8_instead(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t k, const m
   if (o.form != MMP_FORM_AUTO || o.tile || o.force_kblock || o.splits || o.extended_block || o.centered_words)
     return false;
   // INT8 words where they are estimated 10% (and 5 us, a workspace taken and given
-  // back) faster, their k rounded up to whole planes; for outputs at most 128
-  // wide whose k the FP64 words share out as k-ranges, where the estimates err most,
-  // 35%.  Entries of fewer than 18 bits stay: one or two words suffice.  Of 1000
-  // products that the plan gives to FP64 words (m, n to 200000, k to 65536, 5 to 52
-  // bits) 247 move, 1.98 times as fast (geometric mean), 3 of them 3 to 5% slower:
-  // 7187 x 2306 x 37, 52 bits: 328 us on FP64 words, 82 on residues; 139 x 200 x
-  // 1969, 37 bits: 161 and 56.
+  // back) faster, their k rounded up to whole planes; for outputs at most 128 wide
+  // whose k the FP64 words share out as k-ranges, where the estimates err most, 25%.
+  // Entries of fewer than 18 bits stay: one or two words suffice.  Of 1000 products
+  // that the plan gives to FP64 words, by the MFMA and memory peaks (m, n to 200000,
+  // k to 65536, 5 to 52 bits), 130 move, 1.67 times as fast (geometric mean), 2 of
+  // them 3 and 6% slower: 5507 x 7242 x 58, 41 bits: 570 us on FP64 words, 148 on INT8.
   const bool narrow = std::min(m, n) <= 128 && pl.splits > 1;
-  const double limit = (narrow ? 0.65 : 0.9) * fp64_words_us(pl, m, n, k) - 5.0;
+  const double limit = (narrow ? 0.75 : 0.9) * fp64_words_us(pl, m, n, k) - 5.0;
   if (limit < 12.0) return false;  // below any INT8 product's launches
   TunedChoice tuned;               // a measured choice stands
   if (tune_lookup(pl.p, m, n, k, 0, &tuned)) return false;
