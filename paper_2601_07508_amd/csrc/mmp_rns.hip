@@ -450,7 +450,11 @@ bool rns_chosen(uint64_t p, int64_t m, int64_t n, int64_t k, const mmp_opts* opt
   RnsPlan large;
   if (plan_shape<RnsLarge>(nm, m, n, k, &large) && large.us < small.us) *r = large;
   if (r->bytes > kInt8MaxBytes) return false;
-  return r->us < digits_us(m, n, k, digits_for(p));
+  // Where a size is below 1024 the estimates err more, and the residue form has to be
+  // 10% faster by them: without that 14 of 355 such products ran 4 to 21% slower than
+  // on their digits (948^3, 33 bits: 54 us against 45), with it 2, by 4 and 6%.
+  const double margin = std::min(std::min(m, n), k) < 1024 ? 0.9 : 1.0;
+  return r->us < margin * digits_us(m, n, k, digits_for(p));
 }
 
 double int8_us(uint64_t p, int64_t m, int64_t n, int64_t k, const mmp_opts* opts, size_t* bytes) {
@@ -584,7 +588,7 @@ bool rns_crt_chosen(int64_t m, int64_t n, int64_t k, int entry_bits, const uint6
   // Else the digit form's one kernel for the D^2 digit products and all primes.
   // Both in microseconds, fitted to 300 jobs with m, n log-uniform up to 3072,
   // k to 8192, 16 to 62 bits and 3 to 64 primes (within 18% for 80% of them;
-  // choosing by it costs 1.2% over always choosing right).  The residue form
+  // choosing by it costs 5% over always choosing right, 1.2% without the margins below).  The residue form
   // won 214 of them (2048^3, 60 bits, 32 primes: 666 -> 445 us); short k with
   // few bits stays with the digits (2521 x 2750 x 263, 32 bits, 5 primes: 164
   // against 190).
@@ -595,7 +599,10 @@ bool rns_crt_chosen(int64_t m, int64_t n, int64_t k, int entry_bits, const uint6
                         0.037 * (double)rounds * chain + 0.79 * (double)rounds * nprimes + 0.231 * out;
   const int64_t waves = 32 * cdiv(m, 128) * cdiv(n, 128);
   const double residues = 0.7 + 0.894 * c->plan.us + 0.139 * out + nprimes * (0.464 + 0.2 * (double)cdiv(waves, 1024));
-  return residues < digits;
+  // Of those 300 jobs 11 ran 4 to 23% slower in the residue form than the estimates
+  // said, 2 with these margins: from few digits, and where a size is small.
+  const double margin = D <= 4 ? 0.78 : std::min(std::min(m, n), k) <= 700 ? 0.9 : 1.0;
+  return residues < margin * digits;
 }
 
 int launch_rns_crt(const RnsCrt& c, const uint64_t* A, int64_t lda, const uint64_t* B, int64_t ldb, int64_t m, int64_t n,
