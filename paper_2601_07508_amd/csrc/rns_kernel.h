@@ -16,8 +16,8 @@
 //   3. rns_combine_kernel: the N bytes of an output into X mod p by the Chinese
 //      remainder theorem in binary64, C written once.
 // Every step is exact; the bounds stand beside each step.  Measured on one
-// MI355X, digit form -> this form: 4096^3 at 36 bits 1209 -> 804 us, 6001 x 5003
-// x 7013 at 50 bits 7845 -> 3019 us, 512 x 512 x 131072 at 52 bits 1565 -> 1240
+// MI355X, digit form -> this form: 4096^3 at 36 bits 1167 -> 777 us, 6001 x 5003
+// x 7013 at 50 bits 7691 -> 2925 us, 512 x 512 x 131072 at 52 bits 1515 -> 1208
 // us.
 #pragma once
 #include <hip/hip_runtime.h>
