@@ -725,14 +725,15 @@ bool int8_instead(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t k, const m
   if (o.form != MMP_FORM_AUTO || o.tile || o.force_kblock || o.splits || o.extended_block || o.centered_words)
     return false;
   // INT8 words where they are estimated 10% (and 5 us, a workspace taken and given
-  // back) faster, their k rounded up to whole planes; for outputs at most 128 wide
-  // whose k the FP64 words share out as k-ranges, where the estimates err most, 35%.
+  // back) faster, their k rounded up to whole planes; 35% where the estimates err most,
+  // for outputs at most 128 wide whose k the FP64 words share out as k-ranges, and for
+  // k below 256 (5293 x 12481 x 71, 20 bits: 275 us on FP64 words, 325 on digits).
   // Entries of fewer than 18 bits stay: one or two words suffice.  Of 1500 products
   // that the plan gives to FP64 words, by the MFMA and memory peaks (m, n to 200000,
   // k to 65536, 5 to 52 bits), 172 move, 1.65 times as fast (geometric mean), 2 of
   // them 4 and 7% slower: 5507 x 7242 x 58, 41 bits: 570 us on FP64 words, 148 on INT8.
-  const bool narrow = std::min(m, n) <= 128 && pl.splits > 1;
-  const double limit = (narrow ? 0.65 : 0.9) * fp64_words_us(pl, m, n, k) - 5.0;
+  const bool loose = (std::min(m, n) <= 128 && pl.splits > 1) || k < 256;
+  const double limit = (loose ? 0.65 : 0.9) * fp64_words_us(pl, m, n, k) - 5.0;
   if (limit < 12.0) return false;  // below any INT8 product's launches
   TunedChoice tuned;               // a measured choice stands
   if (tune_lookup(pl.p, m, n, k, 0, &tuned)) return false;

@@ -450,10 +450,10 @@ bool rns_chosen(uint64_t p, int64_t m, int64_t n, int64_t k, const mmp_opts* opt
   RnsPlan large;
   if (plan_shape<RnsLarge>(nm, m, n, k, &large) && large.us < small.us) *r = large;
   if (r->bytes > kInt8MaxBytes) return false;
-  // Where a size is below 1024 the estimates err more, and the residue form has to be
-  // 10% faster by them: without that 14 of 355 such products ran 4 to 21% slower than
-  // on their digits (948^3, 33 bits: 54 us against 45), with it 2, by 4 and 6%.
-  const double margin = std::min(std::min(m, n), k) < 1024 ? 0.9 : 1.0;
+  // Where a size is below 1024 the estimates err more, above all with a short k (957^3,
+  // 42 bits: estimated 45 us against 53 on digits, took 55 against 49): the residue
+  // form has to be 20% faster by them there, 10% with m or n below 1024.
+  const double margin = k < 1024 ? 0.8 : std::min(m, n) < 1024 ? 0.9 : 1.0;
   return r->us < margin * digits_us(m, n, k, digits_for(p));
 }
 
