@@ -719,10 +719,8 @@ static double fp64_words_us(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t 
 
 bool int8_instead(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t k, const mmp_opts* opts, mmp_plan_t* out) {
   if (pl.form != MMP_FORM_FP64_WORDS || m <= 0 || n <= 0 || k <= 0 || pl.p < (1u << 18)) return false;
-  mmp_opts o;
-  std::memset(&o, 0, sizeof(o));
-  if (opts) o = *opts;
-  if (o.form != MMP_FORM_AUTO || o.tile || o.force_kblock || o.splits || o.extended_block || o.centered_words)
+  if (opts && (opts->form != MMP_FORM_AUTO || opts->tile || opts->force_kblock || opts->splits ||
+               opts->extended_block || opts->centered_words))
     return false;
   // INT8 words where they are estimated 10% (and 5 us, a workspace taken and given
   // back) faster, their k rounded up to whole planes; 35% where the estimates err most,
@@ -739,6 +737,9 @@ bool int8_instead(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t k, const m
   if (tune_lookup(pl.p, m, n, k, 0, &tuned)) return false;
   size_t residue_bytes;
   if (int8_us(pl.p, m, n, cdiv(k, 64) * 64, opts, &residue_bytes) >= limit) return false;
+  mmp_opts o;
+  std::memset(&o, 0, sizeof(o));
+  if (opts) o = *opts;
   o.form = MMP_FORM_INT8_WORDS;
   if (plan(pl.p, 0, 0, m, n, k, &o, out) != MMP_OK) return false;
   out->workspace_bytes = std::max(out->workspace_bytes, residue_bytes);  // what the estimate counts on
