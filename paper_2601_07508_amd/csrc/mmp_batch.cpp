@@ -36,13 +36,81 @@ struct Planned {
   size_t ws_offset;
   bool residues;  // in the residue form
   RnsPlan rns;
+  Int8Share share;
 };
 
+// FP64-word products of one configuration run together
+using Fp64Key = std::tuple<int, int, int, int>;
+Fp64Key fp64_key(const mmp_plan_t& pl) {
+  return std::make_tuple(pl.u, pl.v, pl.tile, fp64_class(pl.slots, pl.kblock, pl.lazy != 0));
+}
+
+// Products of a batch that their plans give to FP64 words and that are moved to INT8
+// words (`may`: those that may be).  On INT8 words a product fills in beside others
+// in launches that it shares with them, where each FP64 configuration is a launch of
+// its own with the chip mostly idle (40 to 170 us each in a batch of 32 with sizes 64
+// to 4096).  But products bound by reading one large operand pay for its planes (2 of
+// 16384 x 8 x 32768, 25 bits: 2.06 ms on FP64 words, 4.64 on INT8), and small ones of
+// one configuration need one launch instead of two (2 of 64^3: 17 us against 24).
+// So each configuration's launches are compared with what its products take of the
+// chip on INT8 words: all of them, or those that alone take less there.  Where no
+// other product runs on INT8 words anyway, those launches are paid for as well.
+// Over 15000 random batches (2 to 64 products, sizes 1 to 17000, 8 to 52 bits) the
+// choice between all and none by these estimates costs 0.7% over always choosing
+// right; always moving cost 17%, never 59%.
+void move_to_int8(std::vector<Planned>& pj, const std::vector<char>& may, std::vector<char>* moved) {
+  constexpr double kLaunchUs = 3.0;   // a further launch: its host time and the gap before it
+  constexpr double kSharedUs = 24.0;  // the digits' two launches and a workspace
+  std::map<Fp64Key, std::vector<int>> groups;
+  bool others = false;
+  double chain = 0.0, gain = 0.0;
+  for (size_t i = 0; i < pj.size(); i++) {
+    const mmp_job& j = *pj[i].job;
+    if (j.m == 0 || j.n == 0 || j.k == 0) continue;
+    if (pj[i].plan.form == MMP_FORM_FP64_WORDS)
+      groups[fp64_key(pj[i].plan)].push_back((int)i);
+    else
+      others = true;
+  }
+  std::vector<Fp64Load> loads;
+  auto launches_us = [&](const std::vector<int>& g, auto stays) {
+    loads.clear();
+    for (int i : g)
+      if (stays(i)) loads.push_back(fp64_load(pj[i].plan, pj[i].job->m, pj[i].job->n, pj[i].job->k));
+    double us = 0.0;
+    for (size_t c = 0; c < loads.size(); c += kMaxBatch)
+      us += kLaunchUs + fp64_launch_us(pj[g[0]].plan, loads.data() + c, (int)std::min<size_t>(kMaxBatch, loads.size() - c));
+    return us;
+  };
+  for (const auto& kv : groups) {
+    const std::vector<int>& g = kv.second;
+    const double none = launches_us(g, [](int) { return true; });
+    double best = none;
+    int choice = 0;
+    for (int which = 1; which <= 2; which++) {
+      auto moves = [&](int i) {
+        return may[i] && (which == 1 || pj[i].share.us <
+                                            fp64_load(pj[i].plan, pj[i].job->m, pj[i].job->n, pj[i].job->k).share);
+      };
+      double us = launches_us(g, [&](int i) { return !moves(i); });
+      for (int i : g)
+        if (moves(i)) us += pj[i].share.us;
+      if (us >= best) continue;
+      best = us;
+      choice = which;
+      for (int i : g) (*moved)[i] = moves(i);
+    }
+    if (choice == 0) continue;
+    gain += none - best;
+    for (int i : g)
+      if ((*moved)[i]) chain = std::max(chain, pj[i].share.chain_us);
+  }
+  if (!others && gain < kSharedUs + chain) moved->assign(pj.size(), 0);
+}
+
 // together: AUTO products of a batch of two or more are planned for the launches
-// they share.  One on FP64 words would be a launch of its own with the chip mostly
-// idle (40 to 170 us each in a batch of 32 with sizes 64 to 4096); on INT8 words
-// it fills in beside the others.  And each takes the residue form where that is
-// less of the chip's time.
+// they share: on FP64 or INT8 words by move_to_int8, and each on INT8 words in the
+// residue form where that is less of the chip's time.
 int plan_batch(const mmp_job* jobs, int count, const mmp_opts* opts, bool together, std::vector<Planned>* out,
                size_t* ws_total) {
   if (count < 0 || (count > 0 && !jobs)) return MMP_EINVAL;
@@ -56,7 +124,8 @@ int plan_batch(const mmp_job* jobs, int count, const mmp_opts* opts, bool togeth
              !o1.force_kblock && !o1.extended_block && !o1.centered_words;
   out->clear();
   out->reserve(count);
-  double digits_us = 0.0;
+  std::vector<char> may(count, 0), moved(count, 0);
+  bool any = false;
   for (int i = 0; i < count; i++) {
     const mmp_job& j = jobs[i];
     if (int st = check_product_args(j.m, j.n, j.k, j.A, j.lda, j.B, j.ldb, j.C, j.ldc)) return st;
@@ -65,21 +134,28 @@ int plan_batch(const mmp_job* jobs, int count, const mmp_opts* opts, bool togeth
     if (int st = mmp::plan(j.p, j.u, j.v, j.m, j.n, j.k, opts, &pj.plan)) return st;
     if (!fp64_ld_ok(pj.plan, j.lda, j.ldb)) return MMP_EINVAL;
     pj.residues = false;
-    const bool empty = j.m == 0 || j.n == 0 || j.k == 0;
-    if (together && j.u == 0 && !empty) {
+    if (together && j.u == 0 && j.m > 0 && j.n > 0 && j.k > 0) {
+      pj.residues = rns_batch_chosen(j.p, j.m, j.n, j.k, &pj.rns, &pj.share);
       TunedChoice tuned;  // a measured choice stands
-      if (pj.plan.form == MMP_FORM_FP64_WORDS && !tune_lookup(j.p, j.m, j.n, j.k, 0, &tuned)) {
-        mmp_opts o2 = o1;
-        o2.form = MMP_FORM_INT8_WORDS;
-        if (int st = mmp::plan(j.p, 0, 0, j.m, j.n, j.k, &o2, &pj.plan)) return st;
-      }
-      if (pj.plan.form == MMP_FORM_INT8_WORDS) {
-        double us;
-        pj.residues = rns_batch_chosen(j.p, j.m, j.n, j.k, &pj.rns, &us);
-        digits_us += us;
-      }
+      may[i] = pj.plan.form == MMP_FORM_FP64_WORDS && !tune_lookup(j.p, j.m, j.n, j.k, 0, &tuned);
+      any = any || may[i];
     }
     out->push_back(pj);
+  }
+  if (any) move_to_int8(*out, may, &moved);
+  double digits_us = 0.0;
+  for (int i = 0; i < count; i++) {
+    Planned& pj = (*out)[i];
+    const mmp_job& j = jobs[i];
+    if (moved[i]) {
+      mmp_opts o2 = o1;
+      o2.form = MMP_FORM_INT8_WORDS;
+      if (int st = mmp::plan(j.p, 0, 0, j.m, j.n, j.k, &o2, &pj.plan)) return st;
+    }
+    if (pj.plan.form != MMP_FORM_INT8_WORDS)
+      pj.residues = false;
+    else if (together && j.u == 0 && j.m > 0 && j.n > 0 && j.k > 0)
+      digits_us += pj.share.digits_us;
   }
   // Small batches stay whole on their digits, two launches instead of five (16
   // products with sizes 64 to 1000, 75 us of kernels: 87 us against 95).  Residue
@@ -120,11 +196,11 @@ int run_batch(const std::vector<Planned>& pj, const mmp_opts* opts, size_t ws_to
       if (int st = validate_product_entries(j.p, j.m, j.n, j.k, j.A, j.lda, j.B, j.ldb, stream)) return st;
   }
   // FP64-word products, grouped by kernel configuration
-  std::map<std::tuple<int, int, int, int>, std::vector<const Planned*>> groups;
+  std::map<Fp64Key, std::vector<const Planned*>> groups;
   for (const Planned& x : pj) {
     const mmp_job& j = *x.job;
     if (j.m == 0 || j.n == 0 || j.k == 0 || x.plan.form != MMP_FORM_FP64_WORDS) continue;
-    groups[std::make_tuple(x.plan.u, x.plan.v, x.plan.tile, fp64_class(x.plan.slots, x.plan.kblock, x.plan.lazy != 0))].push_back(&x);
+    groups[fp64_key(x.plan)].push_back(&x);
   }
   for (auto& kv : groups) {
     const auto& v = kv.second;

@@ -205,6 +205,14 @@ int launch_int8_batch(const Int8Args* jobs, const int* digits, int njobs, void* 
 // these options is estimated faster on INT8 words, by measured times rather than
 // the plan's peak rates.
 bool int8_instead(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t k, const mmp_opts* opts, mmp_plan_t* out);
+// What a product takes of an FP64 launch, and the estimated microseconds of one
+// launch of `count` products that share pl's configuration.
+struct Fp64Load {
+  int64_t stages, range, items;  // stages of k, of one workgroup's range of it; workgroups
+  double share;                  // microseconds of the whole chip
+};
+Fp64Load fp64_load(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t k);
+double fp64_launch_us(const mmp_plan_t& pl, const Fp64Load* x, int count);
 // Residue form of an INT8 product (rns_kernel.h): n moduli of at most 256,
 // `splits` k-ranges, and a workspace of A's planes, B's planes and the
 // outputs' residue bytes.
@@ -229,13 +237,17 @@ double int8_us(uint64_t p, int64_t m, int64_t n, int64_t k, const mmp_opts* opts
 int launch_rns(const RnsPlan& r, const Int8Args& g, void* stream);
 // Products of a batch: true when this one belongs in the residue form's shared
 // launches rather than the digits', with *r for launch_rns_batch (each product's
-// workspace at g.work).  *digits_us: its estimated time on its digits.
+// workspace at g.work), and what it takes of the chip in either.
 struct RnsBatchJob {
   Int8Args g;
   RnsPlan plan;
 };
 constexpr int kMaxRnsBatch = 64;
-bool rns_batch_chosen(uint64_t p, int64_t m, int64_t n, int64_t k, RnsPlan* r, double* digits_us);
+struct Int8Share {
+  double digits_us, us;  // on its digits without their epilogue; in the faster form
+  double chain_us;       // the digits' chain of one workgroup
+};
+bool rns_batch_chosen(uint64_t p, int64_t m, int64_t n, int64_t k, RnsPlan* r, Int8Share* share);
 int launch_rns_batch(const RnsBatchJob* jobs, int njobs, void* stream);
 // The multi-modular product in the same form: X in `limbs` limbs of base
 // 2^base_bits, which every prime reduces.

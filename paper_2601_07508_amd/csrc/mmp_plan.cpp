@@ -701,20 +701,44 @@ int plan(uint64_t p, int u, int v, int64_t m, int64_t n, int64_t k, const mmp_op
   return plan_impl(p, u, v, m, n, k, opts, out, true);
 }
 
-// FP64 words as planned, in microseconds: a fixed part, the chain of one
-// workgroup's stages, the MFMAs by rounds of 512 workgroups and by the chip's
-// share, the slabs that each tile reads, and a second launch for k-ranges.
-// Fitted (least relative squares) to 474 products with m, n, k log-uniform up to
-// 12000 (k to 65536) and 18 to 52 bits on one MI355X.
-static double fp64_words_us(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t k) {
+Fp64Load fp64_load(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t k) {
   const int64_t terms = (pl.slots <= kBK && pl.kblock < pl.slots) ? (kBK / pl.slots) * pl.kblock : kBK;
-  const int64_t stages = cdiv(k, terms), range = cdiv(stages, pl.splits);
-  const int64_t tm = cdiv(m, pl.bm), tn = cdiv(n, pl.bn), items = tm * tn * pl.splits;
-  const bool shared = fp64_two_groups(pl.u, pl.v, pl.bm, pl.bn, items, stages / pl.splits);
+  const int64_t tm = cdiv(m, pl.bm), tn = cdiv(n, pl.bn);
+  Fp64Load x;
+  x.stages = cdiv(k, terms);
+  x.range = cdiv(x.stages, pl.splits);
+  x.items = tm * tn * pl.splits;
+  x.share = (double)x.items / 512 * pl.u * pl.v * (pl.bm / 32) * (pl.bn / 32) * (0.168 * (double)x.range + 0.62) +
+            0.170e-6 * ((double)tn * m * k + (double)tm * k * n);
+  return x;
+}
+
+// A fixed part, the chain of one workgroup's stages, the MFMAs by rounds of 512
+// workgroups and by the chip's share, the slabs that each tile reads, and a second
+// launch for k-ranges.  Fitted (least relative squares) to 474 single products with
+// m, n, k log-uniform up to 12000 (k to 65536) and 18 to 52 bits on one MI355X; of
+// 12000 launches of 2 to 64 products (m, n, k from 1 to 17000, 8 to 52 bits) it gives
+// 90% within 0.8 to 1.4 of the measured time.
+double fp64_launch_us(const mmp_plan_t& pl, const Fp64Load* x, int count) {
+  int64_t items = 0, least = INT64_MAX, longest = 0;
+  double share = 0.0, staged = 0.0;
+  for (int i = 0; i < count; i++) {
+    items += x[i].items;
+    least = std::min(least, x[i].stages / pl.splits);
+    longest = std::max(longest, x[i].range);
+    share += x[i].share;
+    staged += (double)x[i].items * (double)x[i].range;
+  }
+  const bool shared = fp64_two_groups(pl.u, pl.v, pl.bm, pl.bn, items, least);
   const double work = (double)pl.u * pl.v * (pl.bm / 32) * (pl.bn / 32);
-  return 6.9 + 0.095 * (double)cdiv(range, shared ? 2 : 1) * (pl.u + pl.v) +
-         0.101 * (double)(cdiv(items, 512) * range) * work + (double)items / 512 * work * (0.168 * (double)range + 0.62) +
-         0.170e-6 * ((double)tn * m * k + (double)tm * k * n) + (pl.splits > 1 ? 7.5 : 0.0);
+  return 6.9 + 0.095 * (double)cdiv(longest, shared ? 2 : 1) * (pl.u + pl.v) +
+         0.101 * (double)cdiv(items, 512) * (items > 512 ? staged / (double)items : (double)longest) * work + share +
+         (pl.splits > 1 ? 7.5 : 0.0);
+}
+
+static double fp64_words_us(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t k) {
+  const Fp64Load x = fp64_load(pl, m, n, k);
+  return fp64_launch_us(pl, &x, 1);
 }
 
 bool int8_instead(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t k, const mmp_opts* opts, mmp_plan_t* out) {

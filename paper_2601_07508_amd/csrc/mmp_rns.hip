@@ -474,31 +474,38 @@ int launch_rns(const RnsPlan& r, const Int8Args& g, void* stream) {
   return r.large ? launch_mod_p<RnsLarge>(r, g, g.work, s) : launch_mod_p<RnsSmall>(r, g, g.work, s);
 }
 
-bool rns_batch_chosen(uint64_t p, int64_t m, int64_t n, int64_t k, RnsPlan* r, double* digits_us) {
+bool rns_batch_chosen(uint64_t p, int64_t m, int64_t n, int64_t k, RnsPlan* r, Int8Share* share) {
   using namespace rns;
-  *digits_us = 0.0;
+  *share = Int8Share{0.0, 0.0, 0.0};
   if (m <= 0 || n <= 0 || k <= 0 || std::max(std::max(m, n), k) > 0x7fffffff) return false;
   // the chip's time of this product on its digits, in the launch of the whole batch
   const int D = digits_for(p), bn = D <= 4 ? 64 : 32;
-  const double entries = ((double)m + n) * k;
-  *digits_us = 0.064 / 512 * D * D * (bn / 64.0) * (double)cdiv(m, 64) * cdiv(n, bn) * cdiv(k, 64) +
-               0.233e-6 * entries * (8 + D);
+  const double entries = ((double)m + n) * k, tiles = (double)(cdiv(m, 64) * cdiv(n, bn)), st = (double)cdiv(k, 64);
+  const double products = 0.064 / 512 * D * D * (bn / 64.0) * tiles * st, planes = 0.233e-6 * entries * (8 + D);
+  share->digits_us = products + planes;
+  share->us = products + planes + 0.636 / 512 * D * tiles + 1.96e-6 * (double)m * n;
+  share->chain_us = 0.014 * st * D * D + 0.33 * st;
   const int nm = p < (1u << 16) ? 0 : rns_moduli(std::log2((double)k) + 2.0 * std::log2((double)(p / 2)));
   if (nm == 0) return false;
   RnsPlan small, large;
   if (!plan_shape<RnsSmall>(nm, m, n, k, &small, false) || !plan_shape<RnsLarge>(nm, m, n, k, &large, false)) return false;
   // and by its residues: a large tile's stage takes 0.65 / 256 us, a small one's 0.339 / 512
-  const double st = (double)cdiv(k, 64) * nm;
-  const double tl = 0.65 / 256 * st * (double)cdiv(m, RnsLarge::BM) * cdiv(n, RnsLarge::BN);
-  const double ts = 0.339 / 512 * st * (double)cdiv(m, RnsSmall::BM) * cdiv(n, RnsSmall::BN);
+  const double tl = 0.65 / 256 * st * nm * (double)cdiv(m, RnsLarge::BM) * cdiv(n, RnsLarge::BN);
+  const double ts = 0.339 / 512 * st * nm * (double)cdiv(m, RnsSmall::BM) * cdiv(n, RnsSmall::BN);
   *r = tl < ts ? large : small;
   const double residues = std::min(tl, ts) + 0.233e-6 * entries * (8 + nm) + 0.22e-6 * (double)m * n * (2 * nm + 8);
+  share->us = std::min(share->us, residues);
   // The digits' launch holds the code of every digit count, at 64 x 32 tiles from
-  // five digits on, and runs well below that estimate: batches of 32 and 64
-  // products with sizes 64 to 4096 took 1553 and 1112 us with every product on its
-  // digits, 1154 and 953 with those whose residues take less than 1.3 times the
-  // estimate, 1112 and 924 with 3 times, 1106 and 937 with all.
-  return residues < 3.0 * *digits_us;
+  // five digits on, and its products run well below that estimate: batches of 32 and
+  // 64 products with sizes 64 to 4096 took 1553 and 1112 us with every product on
+  // its digits, 1154 and 953 with those whose residues take less than 1.3 times the
+  // estimate, 1112 and 924 with 3 times, 1106 and 937 with all.  The planes run as
+  // estimated in both forms, so that where they are most of the time, in products
+  // with one narrow side, the digits' smaller ones win (6 of 8 x 4096 x 8192, 36
+  // bits: 880 us against 1420), unless one workgroup's chain of digit products is
+  // longer (4 of 325 x 3 x 32231, 43 bits: 446 us in the residue form, its k-ranges
+  // side by side, 661 on digits).
+  return residues < std::max(3.0 * products + planes, share->chain_us);
 }
 
 int launch_rns_batch(const RnsBatchJob* jobs, int njobs, void* stream) {
