@@ -134,6 +134,7 @@ int plan_batch(const mmp_job* jobs, int count, const mmp_opts* opts, bool togeth
     if (int st = mmp::plan(j.p, j.u, j.v, j.m, j.n, j.k, opts, &pj.plan)) return st;
     if (!fp64_ld_ok(pj.plan, j.lda, j.ldb)) return MMP_EINVAL;
     pj.residues = false;
+    pj.share = Int8Share{0.0, 0.0, 0.0};
     if (together && j.u == 0 && j.m > 0 && j.n > 0 && j.k > 0) {
       pj.residues = rns_batch_chosen(j.p, j.m, j.n, j.k, &pj.rns, &pj.share);
       TunedChoice tuned;  // a measured choice stands
@@ -143,34 +144,37 @@ int plan_batch(const mmp_job* jobs, int count, const mmp_opts* opts, bool togeth
     out->push_back(pj);
   }
   if (any) move_to_int8(*out, may, &moved);
+  // Small batches stay whole on their digits, two launches instead of five (16
+  // products with sizes 64 to 1000, 75 us of kernels: 87 us against 95).
+  constexpr double kSmallBatchUs = 120.0;
+  // Memory that no product's own plan calls for, at most in all: residue planes, and
+  // any planes of products planned on FP64 words.  Beyond it each is as planned.
+  constexpr size_t kMaxExtraBytes = (size_t)8 << 30;
   double digits_us = 0.0;
   for (int i = 0; i < count; i++) {
     Planned& pj = (*out)[i];
+    if (!moved[i] && pj.plan.form != MMP_FORM_INT8_WORDS)
+      pj.residues = false;
+    else if (together && jobs[i].u == 0)
+      digits_us += pj.share.digits_us;
+  }
+  size_t ws = 0, extra = 0;
+  for (int i = 0; i < count; i++) {
+    Planned& pj = (*out)[i];
     const mmp_job& j = jobs[i];
+    if (pj.residues && (digits_us < kSmallBatchUs || extra + pj.rns.bytes > kMaxExtraBytes)) pj.residues = false;
     if (moved[i]) {
       mmp_opts o2 = o1;
       o2.form = MMP_FORM_INT8_WORDS;
-      if (int st = mmp::plan(j.p, 0, 0, j.m, j.n, j.k, &o2, &pj.plan)) return st;
+      mmp_plan_t p8;
+      if (int st = mmp::plan(j.p, 0, 0, j.m, j.n, j.k, &o2, &p8)) return st;
+      if (pj.residues || extra + p8.workspace_bytes <= kMaxExtraBytes) pj.plan = p8;
     }
-    if (pj.plan.form != MMP_FORM_INT8_WORDS)
-      pj.residues = false;
-    else if (together && j.u == 0 && j.m > 0 && j.n > 0 && j.k > 0)
-      digits_us += pj.share.digits_us;
-  }
-  // Small batches stay whole on their digits, two launches instead of five (16
-  // products with sizes 64 to 1000, 75 us of kernels: 87 us against 95).  Residue
-  // planes up to kMaxResidueBytes in all; further products on their digits.
-  constexpr size_t kMaxResidueBytes = (size_t)8 << 30;
-  constexpr double kSmallBatchUs = 120.0;
-  size_t ws = 0, residue_bytes = 0;
-  for (Planned& pj : *out) {
-    const mmp_job& j = *pj.job;
-    if (pj.residues && (digits_us < kSmallBatchUs || residue_bytes + pj.rns.bytes > kMaxResidueBytes))
-      pj.residues = false;
-    if (pj.residues) residue_bytes += pj.rns.bytes;
     pj.ws_offset = ws;
-    if (pj.plan.form == MMP_FORM_INT8_WORDS && j.m > 0 && j.n > 0 && j.k > 0)
-      ws += align_up(pj.residues ? pj.rns.bytes : pj.plan.workspace_bytes);
+    if (pj.plan.form != MMP_FORM_INT8_WORDS || j.m == 0 || j.n == 0 || j.k == 0) continue;
+    const size_t bytes = pj.residues ? pj.rns.bytes : pj.plan.workspace_bytes;
+    if (pj.residues || moved[i]) extra += bytes;
+    ws += align_up(bytes);
   }
   // outputs must not overlap each other
   for (int a = 0; a < count; a++)

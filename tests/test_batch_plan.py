@@ -56,3 +56,10 @@ def test_joins_others_launches():
     alone = workspace([large, (0, 0, 0, P36)])
     assert planned_on_fp64([small]) and alone > 0
     assert workspace([small, small]) == 0 and workspace([large, small]) > alone
+
+
+def test_memory_that_no_plan_calls_for_is_bounded():
+    # faster on INT8 words one and all, 2.6 to 5 GB of planes each
+    dims = [(16384, 1, 32768, P50)] * 16
+    assert planned_on_fp64(dims)
+    assert 0 < workspace(dims) <= (8 << 30) + 16 * 256
