@@ -206,6 +206,15 @@ static bool give_block(int dev, void* ptr, hipStream_t s) {
   return false;
 }
 
+bool capturing(void* stream) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing((hipStream_t)stream, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return cap != hipStreamCaptureStatusNone;
+}
+
 int acquire_workspace(size_t bytes, const mmp_opts* opts, void* stream, void** out, bool* owned) {
   *out = nullptr;
   *owned = false;
@@ -219,14 +228,8 @@ int acquire_workspace(size_t bytes, const mmp_opts* opts, void* stream, void** o
   if (int e = (int)hipGetDevice(&dev)) return hip_status(e);
   if (int e = prepare_pool(dev)) return hip_status(e);
   hipStream_t s = (hipStream_t)stream;
-  if (bytes <= kKeptBlock) {
-    // a capture records its own allocation: the graph may replay at any time
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cap) != hipSuccess)
-      (void)hipGetLastError();
-    else if (cap == hipStreamCaptureStatusNone)
-      *out = take_block(dev, bytes, s);
-  }
+  // a capture records its own allocation: the graph may replay at any time
+  if (bytes <= kKeptBlock && !capturing(stream)) *out = take_block(dev, bytes, s);
   if (!*out) {
     int e = (int)hipMallocAsync(out, bytes, s);
     if (e == (int)hipErrorOutOfMemory) {
@@ -415,12 +418,7 @@ int run_planned(const mmp_plan_t& pl, const mmp_opts* opts, int64_t m, int64_t n
 static bool int8_memory(const mmp_plan_t& p8, const mmp_opts* opts, void* stream) {
   if (opts && opts->workspace)
     return opts->workspace_bytes >= p8.workspace_bytes && (uintptr_t)opts->workspace % 16 == 0;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing((hipStream_t)stream, &cap) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  return cap == hipStreamCaptureStatusNone && p8.workspace_bytes <= kInt8MaxBytes;
+  return !capturing(stream) && p8.workspace_bytes <= kInt8MaxBytes;
 }
 
 int product_async(const mmp_opts* opts, uint64_t p, int u, int v, int64_t m, int64_t n, int64_t k,

@@ -310,12 +310,15 @@ int mm_modp_batched(const mmp_job* jobs, int count, const mmp_opts* opts, void* 
   try {
     std::vector<Planned> pj;
     size_t ws = 0;
-    if (int st = plan_batch(jobs, count, opts, true, &pj, &ws)) return st;
+    // a capture without a workspace records no allocation that the products' own
+    // plans do not call for
+    const bool together = (opts && opts->workspace) || !capturing(stream);
+    if (int st = plan_batch(jobs, count, opts, together, &pj, &ws)) return st;
     // a caller's workspace too small for that (or unaligned): each product as planned on its own
     if (opts && opts->workspace && (opts->workspace_bytes < ws || (uintptr_t)opts->workspace % 16))
       if (int st = plan_batch(jobs, count, opts, false, &pj, &ws)) return st;
     const int st = run_batch(pj, opts, ws, stream);
-    if (st != MMP_ENOMEM || (opts && opts->workspace)) return st;
+    if (st != MMP_ENOMEM || !together || (opts && opts->workspace)) return st;
     // no memory for the shared launches' planes: again with each product's own
     (void)hipGetLastError();
     if (int st2 = plan_batch(jobs, count, opts, false, &pj, &ws)) return st2;

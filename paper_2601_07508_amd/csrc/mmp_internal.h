@@ -312,6 +312,8 @@ size_t span_bytes(int64_t rows, int64_t cols, int64_t ld);
 bool fp64_ld_ok(const mmp_plan_t& pl, int64_t lda, int64_t ldb);
 int check_product_args(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda, const double* B,
                        int64_t ldb, const double* C, int64_t ldc);
+// Whether work on the stream is recorded into a graph (true also when that cannot be told).
+bool capturing(void* stream);
 int acquire_workspace(size_t bytes, const mmp_opts* opts, void* stream, void** out, bool* owned);
 int release_workspace(void* ptr, bool owned, void* stream);
 int validate_product_entries(uint64_t p, int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
