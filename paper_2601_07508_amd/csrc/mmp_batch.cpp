@@ -138,7 +138,7 @@ int plan_batch(const mmp_job* jobs, int count, const mmp_opts* opts, bool togeth
     if (together && j.u == 0 && j.m > 0 && j.n > 0 && j.k > 0) {
       pj.residues = rns_batch_chosen(j.p, j.m, j.n, j.k, &pj.rns, &pj.share);
       TunedChoice tuned;  // a measured choice stands
-      may[i] = pj.plan.form == MMP_FORM_FP64_WORDS && !tune_lookup(j.p, j.m, j.n, j.k, 0, &tuned);
+      may[i] = pj.plan.form == MMP_FORM_FP64_WORDS && !o1.strict_fmod && !tune_lookup(j.p, j.m, j.n, j.k, 0, &tuned);
       any = any || may[i];
     }
     out->push_back(pj);

@@ -743,8 +743,8 @@ static double fp64_words_us(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t 
 
 bool int8_instead(const mmp_plan_t& pl, int64_t m, int64_t n, int64_t k, const mmp_opts* opts, mmp_plan_t* out) {
   if (pl.form != MMP_FORM_FP64_WORDS || m <= 0 || n <= 0 || k <= 0 || pl.p < (1u << 18)) return false;
-  if (opts && (opts->form != MMP_FORM_AUTO || opts->tile || opts->force_kblock || opts->splits ||
-               opts->extended_block || opts->centered_words))
+  if (opts && (opts->form != MMP_FORM_AUTO || opts->tile || opts->strict_fmod || opts->force_kblock ||
+               opts->splits || opts->extended_block || opts->centered_words))
     return false;
   // INT8 words where they are estimated 10% (and 5 us, a workspace taken and given
   // back) faster, their k rounded up to whole planes; 35% where the estimates err most,

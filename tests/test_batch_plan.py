@@ -63,3 +63,10 @@ def test_memory_that_no_plan_calls_for_is_bounded():
     dims = [(16384, 1, 32768, P50)] * 16
     assert planned_on_fp64(dims)
     assert 0 < workspace(dims) <= (8 << 30) + 16 * 256
+
+
+@pytest.mark.parametrize("option", ["strict_fmod", "extended_block", "centered_words"])
+def test_options_of_fp64_words_keep_them(option):
+    dims = [(512, 512, 512, P36)] * 4
+    assert mmp.plan(P36, 512, 512, 512, splits=1, **{option: True})["form"] == mmp.FORM_FP64_WORDS
+    assert workspace(dims) > 0 and workspace(dims, **{option: True}) == 0
