@@ -3,6 +3,7 @@
 // the hipError_t kept per thread for mmp_last_hip_error().
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 #include <vector>
@@ -153,6 +154,14 @@ static void trim(Kept& k, size_t room, hipStream_t s) {
   (void)hipGetLastError();  // hipErrorNotReady from the queries
 }
 
+// Sizes of kept blocks, a quarter of a power of two apart, so that blocks serve
+// other products too and are at most a quarter larger than what was asked for.
+static size_t block_size(size_t bytes) {
+  size_t step = (size_t)1 << 18;  // 1 MB at least
+  while (8 * step <= bytes) step *= 2;
+  return std::max((bytes + step - 1) / step * step, 4 * step);
+}
+
 // A kept block, or null: none free and no room for another.
 static void* take_block(int dev, size_t bytes, hipStream_t s) {
   Kept& k = kept(dev);
@@ -168,12 +177,13 @@ static void* take_block(int dev, size_t bytes, hipStream_t s) {
     best = (int)i;
     wait = !ready;
   }
+  const size_t size = block_size(bytes);
+  // a block many times the need stays free for a larger product while there is room
+  if (best >= 0 && k.blocks[best].bytes > 4 * size && k.total + size <= kKeptTotal) best = -1;
   if (best >= 0 && (!wait || hipStreamWaitEvent(s, k.blocks[best].done, 0) == hipSuccess)) {
     k.blocks[best].busy = true;
     return k.blocks[best].ptr;
   }
-  size_t size = (size_t)1 << 20;  // sizes are powers of two, so that blocks serve other products too
-  while (size < bytes) size *= 2;
   if (k.total + size > kKeptTotal) trim(k, size, s);
   if (k.total + size > kKeptTotal) return nullptr;
   Block b{nullptr, size, nullptr, s, true};

@@ -1,5 +1,6 @@
 """Workspaces kept between calls: results stay exact when calls of different
 sizes share them over several streams and threads, and beside a graph capture."""
+import ctypes
 import sys
 import threading
 
@@ -72,3 +73,33 @@ def test_threads_share_kept_workspaces(problems):
     for t in threads:
         t.join()
     assert not bad
+
+
+def used_memory():
+    """Bytes taken from the device's default memory pool (hipMemPoolAttrUsedMemCurrent), the workspaces' own."""
+    hip, pool, value = mmp.lib(), ctypes.c_void_p(), ctypes.c_uint64()
+    assert hip.hipDeviceGetDefaultMemPool(ctypes.byref(pool), 0) == 0
+    assert hip.hipMemPoolGetAttribute(pool, 7, ctypes.byref(value)) == 0
+    return value.value
+
+
+def test_kept_blocks_fit_what_they_serve():
+    # digit planes of some 137 MB, then of 0.2 MB: neither takes a block much larger
+    p = 1125899906842597
+    say("block sizes")
+    torch.cuda.synchronize()
+    for m, n, k in ((4800, 16, 4096), (64, 64, 200)):
+        A = torch.ones((m, k), dtype=torch.float64, device="cuda")
+        B = torch.ones((k, n), dtype=torch.float64, device="cuda")
+        C = torch.empty((m, n), dtype=torch.float64, device="cuda")
+        need = mmp.plan(p, m, n, k, form=mmp.FORM_INT8_WORDS, splits=1)["workspace_bytes"]
+        before = used_memory()
+        mmp.mm_modp_async(A, B, C, p, form=mmp.FORM_INT8_WORDS, splits=1)
+        torch.cuda.synchronize()
+        assert bool((C == k).all())
+        grown = used_memory() - before
+        say(m, n, k, need, grown)
+        assert grown <= max(1 << 20, need + need // 4)
+        mmp.mm_modp_async(A, B, C, p, form=mmp.FORM_INT8_WORDS, splits=1)  # and takes it again
+        torch.cuda.synchronize()
+        assert used_memory() - before == grown
