@@ -496,6 +496,14 @@ const char *mmp_strerror(int status);
 /* The hipError_t of the last MMP_EHIP on this thread (0 if none). */
 int mmp_last_hip_error(void);
 
+/* Workspaces that the library allocates (calls without mmp_opts.workspace, the
+ * server) are kept between calls, up to 2 GiB per device; larger ones go back to
+ * the device's default memory pool, which is told to keep what is freed.  This
+ * gives all of them that no running call holds back to the current device, after
+ * waiting for the work that used them, so that other allocators can have the
+ * memory.  Not while a stream of the calling thread is being captured. */
+int mmp_release_workspaces(void);
+
 /* ---------------------------------------------------------------- timers */
 
 /* Per-phase kernel time.  When enabled, every launch the library makes is

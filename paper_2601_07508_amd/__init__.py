@@ -81,6 +81,8 @@ _lib.mmp_strerror.argtypes = [_int]
 _lib.mmp_strerror.restype = ctypes.c_char_p
 _lib.mmp_last_hip_error.argtypes = []
 _lib.mmp_last_hip_error.restype = _int
+_lib.mmp_release_workspaces.argtypes = []
+_lib.mmp_release_workspaces.restype = _int
 
 
 _lib.mm_modp_batched.argtypes = [ctypes.POINTER(MmpJob), _int, ctypes.POINTER(MmpOpts), _vp]
@@ -163,6 +165,11 @@ def timers_read(reset: bool = True) -> dict:
 def lib() -> ctypes.CDLL:
     """The loaded C library (for tests of the raw C-ABI)."""
     return _lib
+
+
+def release_workspaces() -> None:
+    """Gives the workspaces kept between calls back to the device (see mmp_release_workspaces)."""
+    _check(_lib.mmp_release_workspaces(), "mmp_release_workspaces")
 
 
 def strerror(status: int) -> str:

@@ -112,8 +112,8 @@ int prepare_pool(int dev) {
 // or one last returned on a stream of its own handle, and then its stream waits
 // for the event (nothing to wait for on the same stream; the order where a handle
 // names another stream by now).  The host never waits.  The blocks come from the
-// device's memory pool and go back to it when others need the room or an
-// allocation fails.
+// device's memory pool and go back to it when others need the room, an allocation
+// fails or mmp_release_workspaces is called.
 constexpr size_t kKeptBlock = (size_t)256 << 20, kKeptTotal = (size_t)2 << 30;
 
 struct Block {
@@ -160,6 +160,37 @@ static size_t block_size(size_t bytes) {
   size_t step = (size_t)1 << 18;  // 1 MB at least
   while (8 * step <= bytes) step *= 2;
   return std::max((bytes + step - 1) / step * step, 4 * step);
+}
+
+// Gives every kept block of the device that no call holds back to its memory pool,
+// after the work that used it, and what the pool has free to the device.
+static int give_back(int dev) {
+  hipStream_t s;
+  if (int e = (int)hipStreamCreateWithFlags(&s, hipStreamNonBlocking)) return e;
+  int e = 0;
+  {
+    Kept& k = kept(dev);
+    std::lock_guard<std::mutex> lk(k.mu);
+    for (size_t i = 0; i < k.blocks.size() && !e;) {
+      Block& b = k.blocks[i];
+      if (b.busy) {
+        i++;
+        continue;
+      }
+      e = (int)hipStreamWaitEvent(s, b.done, 0);
+      if (!e) e = (int)hipFreeAsync(b.ptr, s);
+      if (e) break;
+      (void)hipEventDestroy(b.done);
+      k.total -= b.bytes;
+      k.blocks.erase(k.blocks.begin() + i);
+    }
+  }
+  const int e2 = (int)hipStreamSynchronize(s);
+  const int e3 = (int)hipStreamDestroy(s);
+  hipMemPool_t pool;
+  if (!e) e = e2 ? e2 : e3;
+  if (!e) e = (int)hipDeviceGetDefaultMemPool(&pool, dev);
+  return e ? e : (int)hipMemPoolTrimTo(pool, 0);
 }
 
 // A kept block, or null: none free and no room for another.
@@ -255,6 +286,12 @@ int acquire_workspace(size_t bytes, const mmp_opts* opts, void* stream, void** o
   }
   *owned = true;
   return MMP_OK;
+}
+
+int give_back_workspaces() {
+  int dev = 0;
+  if (int e = (int)hipGetDevice(&dev)) return e;
+  return give_back(dev);
 }
 
 int release_workspace(void* ptr, bool owned, void* stream) {
@@ -501,6 +538,14 @@ const char* mmp_strerror(int status) {
 }
 
 int mmp_last_hip_error(void) { return g_last_hip_error; }
+
+int mmp_release_workspaces(void) {
+  try {
+    return hip_status(mmp::give_back_workspaces());
+  } catch (...) {
+    return MMP_EINVAL;
+  }
+}
 
 int mmp_plan(uint64_t p, int u, int v, int64_t m, int64_t n, int64_t k, const mmp_opts* opts,
              mmp_plan_t* out) {

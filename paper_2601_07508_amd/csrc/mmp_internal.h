@@ -316,6 +316,7 @@ int check_product_args(int64_t m, int64_t n, int64_t k, const double* A, int64_t
 bool capturing(void* stream);
 int acquire_workspace(size_t bytes, const mmp_opts* opts, void* stream, void** out, bool* owned);
 int release_workspace(void* ptr, bool owned, void* stream);
+int give_back_workspaces();  // mmp_release_workspaces; a hipError_t value
 int validate_product_entries(uint64_t p, int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
                              const double* B, int64_t ldb, void* stream);
 int validate_integer_entries(int bits, int64_t m, int64_t n, int64_t k, const uint64_t* A, int64_t lda,

@@ -103,3 +103,48 @@ def test_kept_blocks_fit_what_they_serve():
         mmp.mm_modp_async(A, B, C, p, form=mmp.FORM_INT8_WORDS, splits=1)  # and takes it again
         torch.cuda.synchronize()
         assert used_memory() - before == grown
+
+
+def test_kept_blocks_are_bounded_and_given_back():
+    # eleven streams, each behind work of its own, take blocks of some 240 MB: the
+    # last ones find 2 GiB taken, and a later small block makes room for itself
+    p, m, n, k = 1125899906842597, 8192, 4, 4096
+    A = torch.randint(0, p, (m, k), dtype=torch.int64, device="cuda").double()
+    B = torch.randint(0, p, (k, n), dtype=torch.int64, device="cuda").double()
+    want = torch.from_numpy(oracle.mm_modp(p, A.cpu().numpy().astype(np.uint64),
+                                           B.cpu().numpy().astype(np.uint64)).astype(np.float64)).cuda()
+    busy = torch.randn(4096, 4096, device="cuda")
+    streams = [torch.cuda.Stream() for _ in range(11)]
+    outs = [torch.full((m, n), -1.0, dtype=torch.float64, device="cuda") for _ in streams]
+    torch.cuda.synchronize()
+    mmp.release_workspaces()
+    start = used_memory()
+    assert mmp.plan(p, m, n, k, form=mmp.FORM_INT8_WORDS, splits=1)["workspace_bytes"] > 224 << 20
+    say("eleven streams")
+    for s, C in zip(streams, outs):
+        with torch.cuda.stream(s):
+            for _ in range(20):
+                busy @ busy
+        mmp.mm_modp_async(A, B, C, p, form=mmp.FORM_INT8_WORDS, splits=1, stream=s)
+    torch.cuda.synchronize()
+    assert all(torch.equal(C, want) for C in outs)
+    held = used_memory() - start
+    say("held", held)
+    assert 7 * (224 << 20) < held <= 2 << 30
+    small = torch.ones((64, 64), dtype=torch.float64, device="cuda")
+    for _ in range(2):
+        for shape in ((8192, 4, 2000), (64, 64, 64)):
+            X = torch.ones((shape[0], shape[2]), dtype=torch.float64, device="cuda")
+            Y = torch.ones((shape[2], shape[1]), dtype=torch.float64, device="cuda")
+            C = torch.empty((shape[0], shape[1]), dtype=torch.float64, device="cuda")
+            mmp.mm_modp_async(X, Y, C, p, form=mmp.FORM_INT8_WORDS, splits=1)
+            torch.cuda.synchronize()
+            assert bool((C == shape[2]).all())
+            assert used_memory() - start <= 2 << 30
+    assert used_memory() > start
+    mmp.release_workspaces()
+    assert used_memory() == start
+    C.copy_(small)
+    mmp.mm_modp_async(small, small, C, p, form=mmp.FORM_INT8_WORDS)
+    torch.cuda.synchronize()
+    assert bool((C == 64).all())
