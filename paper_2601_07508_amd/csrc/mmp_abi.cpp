@@ -269,8 +269,11 @@ int acquire_workspace(size_t bytes, const mmp_opts* opts, void* stream, void** o
   if (int e = (int)hipGetDevice(&dev)) return hip_status(e);
   if (int e = prepare_pool(dev)) return hip_status(e);
   hipStream_t s = (hipStream_t)stream;
-  // a capture records its own allocation: the graph may replay at any time
-  if (bytes <= kKeptBlock && !capturing(stream)) *out = take_block(dev, bytes, s);
+  // a capture records its own allocation: the graph may replay at any time.  And
+  // while the caller has an error of its own pending, which the events' queries
+  // would replace, the call allocates, and its launches find that error.
+  if (bytes <= kKeptBlock && hipPeekAtLastError() == hipSuccess && !capturing(stream))
+    *out = take_block(dev, bytes, s);
   if (!*out) {
     int e = (int)hipMallocAsync(out, bytes, s);
     if (e == (int)hipErrorOutOfMemory) {

@@ -148,3 +148,30 @@ def test_kept_blocks_are_bounded_and_given_back():
     mmp.mm_modp_async(small, small, C, p, form=mmp.FORM_INT8_WORDS)
     torch.cuda.synchronize()
     assert bool((C == 64).all())
+
+
+def test_callers_pending_error_is_not_swallowed(problems):
+    # a kept block whose event is still pending on another stream, queried and passed over
+    p, A, B, want, kw = problems[2]
+    hip = mmp.lib()
+    first, second = torch.cuda.Stream(), torch.cuda.Stream()
+    C, D = torch.empty_like(want), torch.empty_like(want)
+    busy = torch.randn(4096, 4096, device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(first):
+        for _ in range(20):
+            busy @ busy
+    mmp.mm_modp_async(A, B, C, p, stream=first, **kw)
+    assert hip.hipSetDevice(4096) != 0  # refused by the host: the caller's error
+    say("pending error")
+    try:
+        mmp.mm_modp_async(A, B, D, p, stream=second, **kw)
+        seen = False
+    except mmp.MmpError as e:
+        seen = "EHIP" in str(e)
+    seen = hip.hipGetLastError() != 0 or seen
+    torch.cuda.synchronize()
+    assert seen
+    mmp.mm_modp_async(A, B, D, p, stream=second, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(C, want) and torch.equal(D, want)
