@@ -116,6 +116,15 @@ int prepare_pool(int dev) {
 // fails or mmp_release_workspaces is called.
 constexpr size_t kKeptBlock = (size_t)256 << 20, kKeptTotal = (size_t)2 << 30;
 
+// The calling thread's stream capture mode while kept blocks are looked at: with the
+// default one, the queries and allocations here invalidated a capture that another
+// thread had open in global mode, with which they have nothing to do.
+struct Relaxed {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 struct Block {
   void* ptr;
   size_t bytes;
@@ -195,6 +204,7 @@ static int give_back(int dev) {
 
 // A kept block, or null: none free and no room for another.
 static void* take_block(int dev, size_t bytes, hipStream_t s) {
+  Relaxed relaxed;
   Kept& k = kept(dev);
   std::lock_guard<std::mutex> lk(k.mu);
   int best = -1;
@@ -234,6 +244,7 @@ static void* take_block(int dev, size_t bytes, hipStream_t s) {
 
 // True when ptr is a kept block; returns it for work after what is queued on s.
 static bool give_block(int dev, void* ptr, hipStream_t s) {
+  Relaxed relaxed;
   Kept& k = kept(dev);
   std::lock_guard<std::mutex> lk(k.mu);
   for (Block& b : k.blocks) {

@@ -2,6 +2,7 @@
 and replays beside eager calls that take and return the kept workspaces."""
 import ctypes
 import sys
+import threading
 
 import numpy as np
 import pytest
@@ -83,3 +84,83 @@ def test_batch_on_fp64_words_records_kernels_alone():
         mmp.mm_modp_batched(jobs)  # eager, on INT8 words
         torch.cuda.synchronize()
         assert all(torch.equal(C, want) for _, _, C, _, want in items)
+
+
+def test_products_that_need_a_workspace_beside_eager_calls():
+    # a captured call allocates for its graph alone; eager calls of the same sizes take
+    # and return kept workspaces between the replays, on the same stream and others
+    items = [problem(40, P50, 90, 70, 9000), problem(41, P36, 300, 200, 700)]
+    kws = [{}, {"form": mmp.FORM_INT8_WORDS}]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+
+    def eager(rounds):
+        for r in range(rounds):
+            for (A, B, C, p, _), kw in zip(items, kws):
+                mmp.mm_modp_async(A, B, C, p, stream=streams[r % 2], **kw)
+        for s in streams:
+            s.synchronize()
+
+    eager(2)
+    graphs = []
+    for (A, B, C, p, want), kw in zip(items, kws):
+        assert mmp.plan(p, *C.shape, A.shape[1], **kw)["workspace_bytes"] > 0
+        g = capture(lambda s: mmp.mm_modp_async(A, B, C, p, stream=s, **kw))
+        say("product capture", node_types(g))
+        graphs.append(g)
+    for rep in range(3):
+        for g, (A, B, C, p, want) in zip(graphs, items):
+            say("replay", rep)
+            C.fill_(-2.0)
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(C, want)
+        for *_, C, _p, _w in items:
+            C.fill_(-3.0)
+        torch.cuda.synchronize()
+        eager(4)
+        assert all(torch.equal(C, want) for _, _, C, _, want in items)
+
+
+def test_another_threads_calls_during_a_capture():
+    # a capture in global mode refuses what other threads must not do meanwhile; calls
+    # that query, take and return kept workspaces are not among it
+    A, B, C, p, want = problem(50, P50, 256, 256, 512)
+    X, Y, _, q, expect = problem(51, P36, 300, 200, 700)
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    outs = [torch.full_like(expect, -1.0) for _ in range(24)]
+    ws = torch.empty(1 << 26, dtype=torch.uint8, device="cuda")
+    busy = torch.randn(2048, 2048, device="cuda")
+    dst = torch.empty_like(busy)
+    torch.cuda.synchronize()
+    errors = []
+
+    def calls():
+        try:
+            for i, D in enumerate(outs):
+                mmp.mm_modp_async(X, Y, D, q, stream=streams[i % 2], form=mmp.FORM_INT8_WORDS)
+        except Exception as e:  # reported below, in the test's own thread
+            errors.append(e)
+
+    with torch.cuda.stream(streams[0]):
+        for _ in range(20):
+            torch.mm(busy, busy, out=dst)
+
+    def body(s):
+        t = threading.Thread(target=calls)
+        mmp.mm_modp_async(A, B, C, p, workspace=ws, stream=s)
+        t.start()
+        t.join()
+        mmp.mm_modp_async(A, B, C, p, workspace=ws, stream=s)
+
+    say("another thread during a capture")
+    g = capture(body)
+    torch.cuda.synchronize()
+    assert not errors, errors
+    assert all(torch.equal(D, expect) for D in outs)
+    for rep in range(3):
+        C.fill_(-2.0)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(C, want)
