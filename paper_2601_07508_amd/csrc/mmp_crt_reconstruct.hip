@@ -26,6 +26,7 @@
 #include <atomic>
 #include <cstdint>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "mmp_internal.h"
@@ -147,16 +148,29 @@ constexpr int kConWaves = 8;
 constexpr int64_t kConLdsMax = 160 * 1024;
 constexpr int kConRow = 80;           // scratch bytes per entry: 16 sums, padded
 
+// Bytes of the digits of 8 KS + 1 constants, each of at most 51 KS + 1 (a modulus
+// has 50.5 bits), or all that the arguments leave room for.  Sized by the k-steps:
+// with the largest table in every launch, 14 KB of arguments, calls of 5 and 6 moduli
+// and up to 2^19 entries took 15.3 and 16.3 us, more than Garner's kernel (14.8 and
+// 16.0), with their own 14.5 and 15.5.
+constexpr int con_digit_bytes(int ksteps) {
+  const int all = (8 * ksteps + 1) * (51 * ksteps + 1);
+  return ((all < kConDigitBytes ? all : kConDigitBytes) + 15) / 16 * 16;
+}
+
+template <int KS>
 struct ConArgs {
-  const double* C[kConMaxModuli];
-  double p[kConMaxModuli], q[kConMaxModuli], inv[kConMaxModuli];
+  const double* C[8 * KS];
+  double p[8 * KS], q[8 * KS], inv[8 * KS];
   int64_t ldc, m, n, ldo;
   uint64_t* out;
   int s, limbs;
   int digits;     // signed base-256 digits of M and of each M / p_t
   int col_tiles;  // 16 output bytes each: the digits' products and M's limbs
-  int8_t dig[kConDigitBytes];  // [s + 1][digits]: the M / p_t, then M
+  int8_t dig[con_digit_bytes(KS)];  // [s + 1][digits]: the M / p_t, then M
 };
+
+static_assert(sizeof(ConArgs<1>) < 1024 && sizeof(ConArgs<6>) < 16384, "as little as a launch has to carry");
 
 // LDS: the constants as MFMA operands, [column tile][k-step][1 KB]; each
 // wave's sums, 64 entries of 16; the moduli's p, q, inverse.
@@ -179,7 +193,7 @@ inline size_t con_lds(int ksteps, int col_tiles) {
 //   sums: |sum| <= 8 48 2^14 < 2^22.6, so two neighbouring bytes' sums combine
 //     in int32, and 32 bits of a limb take one 64-bit addition with the carry.
 template <int KS>
-__global__ __launch_bounds__(64 * kConWaves, 2) void crt_contract_kernel(const ConArgs a) {
+__global__ __launch_bounds__(64 * kConWaves, 2) void crt_contract_kernel(const ConArgs<KS> a) {
   extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
   const int tid = threadIdx.x, lane = tid & 63, q4 = lane >> 4, r16 = lane & 15;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -410,7 +424,7 @@ int limbs_of_product(const uint64_t* p, int lo, int hi) {
 }
 
 template <int KS>
-int launch_contract(const ConArgs& a, void* stream) {
+int launch_contract(const ConArgs<KS>& a, void* stream) {
   const int64_t units = (a.m * a.n + 63) / 64;
   const size_t shmem = con_lds(KS, a.col_tiles);
   static std::atomic<int> ready[64];  // per device: the LDS limit is raised
@@ -484,43 +498,47 @@ extern "C" int mmp_crt_reconstruct(const double* const* C, int64_t ldc, const ui
     // the contraction, where its constants fit the kernel arguments and LDS
     const int D = (M.bits() + 1) / 8 + 1;
     const int ksteps = (nmoduli + 7) / 8, col_tiles = (std::max(D + 6, 8 * lm) + 15) / 16;
-    if (nmoduli >= kConMinModuli && nmoduli <= kConMaxModuli && (nmoduli + 1) * D <= kConDigitBytes &&
+    if (nmoduli >= kConMinModuli && nmoduli <= kConMaxModuli && (nmoduli + 1) * D <= con_digit_bytes(ksteps) &&
         (int64_t)con_lds(ksteps, col_tiles) <= kConLdsMax) {
-      ConArgs a;
-      std::memset(&a, 0, offsetof(ConArgs, dig));
-      a.s = nmoduli;
-      a.limbs = limbs;
-      a.ldc = ldc;
-      a.m = m;
-      a.n = n;
-      a.ldo = ldo;
-      a.out = out;
-      a.digits = D;
-      a.col_tiles = col_tiles;
-      std::vector<Big> after(nmoduli + 1);  // p_t ... p_{s-1}
-      for (int t = nmoduli - 1; t >= 0; t--) {
-        after[t] = after[t + 1];
-        after[t].mul(moduli[t]);
-      }
-      Big before;
-      for (int t = 0; t < nmoduli; t++) {
-        const uint64_t p = moduli[t], inv = rest_inv[t];
-        a.C[t] = C[t];
-        a.p[t] = (double)p;
-        a.q[t] = 1.0 / (double)p;
-        a.inv[t] = 2 * inv > p ? (double)((int64_t)inv - (int64_t)p) : (double)inv;
-        signed_digits(product(before, after[t + 1]), D, a.dig + t * D);
-        before.mul(p);
-      }
-      signed_digits(M, D, a.dig + nmoduli * D);
+      auto run = [&](auto steps) {
+        constexpr int KS = decltype(steps)::value;
+        ConArgs<KS> a;
+        std::memset(&a, 0, offsetof(ConArgs<KS>, dig));
+        a.s = nmoduli;
+        a.limbs = limbs;
+        a.ldc = ldc;
+        a.m = m;
+        a.n = n;
+        a.ldo = ldo;
+        a.out = out;
+        a.digits = D;
+        a.col_tiles = col_tiles;
+        std::vector<Big> after(nmoduli + 1);  // p_t ... p_{s-1}
+        for (int t = nmoduli - 1; t >= 0; t--) {
+          after[t] = after[t + 1];
+          after[t].mul(moduli[t]);
+        }
+        Big before;
+        for (int t = 0; t < nmoduli; t++) {
+          const uint64_t p = moduli[t], inv = rest_inv[t];
+          a.C[t] = C[t];
+          a.p[t] = (double)p;
+          a.q[t] = 1.0 / (double)p;
+          a.inv[t] = 2 * inv > p ? (double)((int64_t)inv - (int64_t)p) : (double)inv;
+          signed_digits(product(before, after[t + 1]), D, a.dig + t * D);
+          before.mul(p);
+        }
+        signed_digits(M, D, a.dig + nmoduli * D);
+        return launch_contract<KS>(a, stream);
+      };
       int e;
       switch (ksteps) {
-        case 1: e = launch_contract<1>(a, stream); break;
-        case 2: e = launch_contract<2>(a, stream); break;
-        case 3: e = launch_contract<3>(a, stream); break;
-        case 4: e = launch_contract<4>(a, stream); break;
-        case 5: e = launch_contract<5>(a, stream); break;
-        default: e = launch_contract<6>(a, stream); break;
+        case 1: e = run(std::integral_constant<int, 1>{}); break;
+        case 2: e = run(std::integral_constant<int, 2>{}); break;
+        case 3: e = run(std::integral_constant<int, 3>{}); break;
+        case 4: e = run(std::integral_constant<int, 4>{}); break;
+        case 5: e = run(std::integral_constant<int, 5>{}); break;
+        default: e = run(std::integral_constant<int, 6>{}); break;
       }
       return hip_status(e);
     }
