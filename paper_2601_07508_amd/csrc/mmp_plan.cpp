@@ -687,10 +687,8 @@ static int plan_impl(uint64_t p, int u, int v, int64_t m, int64_t n, int64_t k, 
   out->est_seconds = fp64_seconds(m, n, k, bu * bv, bk.cost);
   out->splits = o.splits ? o.splits : default_splits(*out, m, n, k);
   out->workspace_bytes = out->splits > 1 ? 8 * (size_t)out->splits * (size_t)m * (size_t)n : 0;
-  RnsPlan rp;
   if (o.form == MMP_FORM_AUTO && u == 0 && o.force_kblock == 0 && o.tile == 0 && !extended && !centered &&
-      (int8_seconds(m, n, k, d8) < out->est_seconds ||
-       (rns_chosen(p, m, n, k, &o, &rp) && 1e-6 * rp.us < out->est_seconds))) {
+      int8_seconds(m, n, k, d8) < out->est_seconds) {
     std::memset(out, 0, sizeof(*out));
     return plan_int8();
   }
