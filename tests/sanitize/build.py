@@ -1,7 +1,8 @@
 """Sanitizer builds of the library's host code plus tests/sanitize/host_driver.cpp.
 
 The host-side sources (the planner, the C-ABI checks, batches, the server,
-the tuner, the timers, the fixed-workspace entry point) are compiled with
+the tuner, the timers, the fixed-workspace entry point, the residue form's
+planning and tables, the reconstruction's constants) are compiled with
 AddressSanitizer + UndefinedBehaviorSanitizer ("asan") or ThreadSanitizer
 ("tsan"); the kernel sources are linked from the product build
 (_build/mmp, written by paper_2601_07508_amd/build.py) as they are, since
@@ -25,6 +26,10 @@ SAN = {
     "asan": ["address", "undefined"],
     "tsan": ["thread"],
 }
+
+
+# sources of kernels with host code of some size beside them
+HOST_SIDE_HIP = {"mmp_static.hip", "mmp_rns.hip", "mmp_crt_reconstruct.hip"}
 
 
 def _lib_sources():
@@ -66,7 +71,7 @@ def build(kind, jobs=8):
         open(stamp, "w").write(key)
         return obj
 
-    host_side = [j for j in _lib_sources() if j[0].endswith(".cpp") or os.path.basename(j[0]) == "mmp_static.hip"]
+    host_side = [j for j in _lib_sources() if j[0].endswith(".cpp") or os.path.basename(j[0]) in HOST_SIDE_HIP]
     kernels = [os.path.join(ROOT, "_build", "mmp", j[2]) for j in _lib_sources() if j not in host_side]
     missing = [o for o in kernels if not os.path.exists(o)]
     if missing:

@@ -2,7 +2,8 @@
 // UndefinedBehaviorSanitizer, ThreadSanitizer).  Test infrastructure: it
 // touches no GPU.  It drives the planner, the INT8 block bound, the
 // footprint, the argument checks of the product entry points (refused on the
-// host before any device call) and a dry-run request server fed by several
+// host before any device call), the workspace queries, the reconstruction's
+// constants up to a launch that fails and a dry-run request server fed by several
 // submitting threads, with one more server whose launches fail on the host.
 #include <cstdio>
 #include <cstdlib>
@@ -100,6 +101,80 @@ static void argument_errors() {
                      nullptr) == MMP_EINVAL);
 }
 
+// The batch's and the multi-modular product's planning (residue form included), from
+// several threads: the tables of the moduli are made by the first that needs them.
+static void workspaces() {
+  std::vector<std::thread> th;
+  for (int t = 0; t < 4; t++)
+    th.emplace_back([t] {
+      const uint64_t primes[] = {251, 65521, 2147483647ull, 68719476731ull, 1125899906842597ull, 4503599627370449ull};
+      for (int i = 0; i < 60; i++) {
+        const int count = 1 + (i * 5 + t) % 70;
+        std::vector<mmp_job> jobs(count);
+        uintptr_t at = (uintptr_t)1 << 32;
+        for (int c = 0; c < count; c++) {
+          mmp_job& j = jobs[c];
+          std::memset(&j, 0, sizeof(j));
+          j.p = primes[(i + c) % 6];
+          j.m = (c * 97 + i * 31) % (i % 7 == 0 ? 9000 : 700);
+          j.n = 1 + (c * 53 + i * 17) % (i % 5 == 0 ? 3000 : 300);
+          j.k = (c * 71 + t) % (i % 3 == 0 ? 30000 : 600);
+          j.A = (const double*)at;
+          j.lda = j.k;
+          at += 8 * (uintptr_t)(j.m * j.k) + 4096;
+          j.B = (const double*)at;
+          j.ldb = j.n;
+          at += 8 * (uintptr_t)(j.k * j.n) + 4096;
+          j.C = (double*)at;
+          j.ldc = j.n;
+          at += 8 * (uintptr_t)(j.m * j.n) + 4096;
+        }
+        for (int strict = 0; strict < 2; strict++) {
+          mmp_opts o;
+          std::memset(&o, 0, sizeof(o));
+          o.strict_fmod = strict;
+          EXPECT(mmp_workspace_batched(jobs.data(), count, &o) < ((size_t)1 << 40));
+        }
+        for (int bits = 1; bits <= 62; bits += 1 + i % 4)
+          EXPECT(mmp_workspace_crt(1 + 37 * i, 1 + 29 * t, 1 + 1000 * (int64_t)i * i, bits, 1 + i, nullptr) > 0);
+      }
+    });
+  for (auto& x : th) x.join();
+}
+
+// Reconstructions up to their launch, which no device takes: nothing of this is run
+// where there is one, for the addresses are no memory.
+extern "C" int hipGetDeviceCount(int*);
+static void reconstruction_constants() {
+  int devices = 0;
+  if (hipGetDeviceCount(&devices) == 0 && devices > 0) return;
+  std::vector<uint64_t> moduli;  // pairwise coprime, the widest that there are
+  for (uint64_t x = ((uint64_t)1 << 52) / 3; moduli.size() < 48; x--) {
+    bool coprime = true;
+    for (uint64_t q : moduli) {
+      uint64_t a = x, b = q;
+      while (b) {
+        const uint64_t r = a % b;
+        a = b;
+        b = r;
+      }
+      coprime = coprime && a == 1;
+    }
+    if (coprime) moduli.push_back(x);
+  }
+  const double* C[48];
+  for (int i = 0; i < 48; i++) C[i] = (const double*)((uintptr_t)0x10000000 + (uintptr_t)i * 0x10000);
+  uint64_t* out = (uint64_t*)(uintptr_t)0x40000000;
+  for (int s : {5, 8, 9, 16, 24, 31, 40, 43}) {
+    EXPECT(mmp_crt_reconstruct(C, 5, moduli.data(), s, 4, 5, out, 5, 52, nullptr) < 0);
+    EXPECT(mmp_crt_reconstruct(C, 5, moduli.data(), s, 4, 5, out, 5, 1, nullptr) == MMP_EINVAL);
+    std::vector<uint64_t> twice(moduli.begin(), moduli.begin() + s);
+    twice[s - 1] = 2 * (twice[0] / 2);
+    twice[0] = 4;
+    EXPECT(mmp_crt_reconstruct(C, 5, twice.data(), s, 4, 5, out, 5, 52, nullptr) == MMP_EINVAL);
+  }
+}
+
 static void dry_run_server() {
   mmp_server* srv = nullptr;
   EXPECT(mmp_server_create(&srv, 0, (size_t)8 << 30, 16, MMP_SERVER_DRY_RUN) == MMP_OK);
@@ -179,6 +254,8 @@ int main() {
   planner();
   int8_bounds();
   argument_errors();
+  workspaces();
+  reconstruction_constants();
   dry_run_server();
   std::printf("host driver: %d failures\n", failures);
   return failures ? 1 : 0;
