@@ -5,6 +5,7 @@ import ctypes
 
 import pytest
 
+pytest.importorskip("torch")  # first, so that the library takes the HIP runtime that torch brings
 mmp = pytest.importorskip("paper_2601_07508_amd")
 
 P25, P36, P50 = 33554393, 68719476731, 1125899906842597
