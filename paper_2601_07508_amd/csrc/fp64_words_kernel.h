@@ -306,10 +306,10 @@ __global__ __launch_bounds__(kThreads * G, 2) void fp64_words_kernel(const Fp64B
   // Stages are loaded in order, each through register slot (stage - s_begin) %
   // AHEAD; what its resources need is kept and moved on: formed anew, it read the
   // arguments again (the barriers clobber memory) and multiplied 64-bit integers in
-  // every stage, 3 to 9% of the time (1024^3, (2,3): 242 -> 224 us; 4096 x 4096 x 2048,
-  // (1,3): 3810 -> 3627).  Stages past the range load through
-  // resources of no bytes (zeros, no access), so that the waits before a slot's use
-  // count the same loads on every path.
+  // every stage: 1024^3, (2,3): 242 -> 224 us; 4096 x 4096 x 2048, (1,3): 3810 -> 3627;
+  // 8192^3, (2,2), where the other wave of a SIMD covers it, 0.5%, what runs differ by.
+  // Stages past the range load through resources of no bytes (zeros, no access), so
+  // that the waits before a slot's use count the same loads on every path.
   double ra[AHEAD][NA], rb[AHEAD][NB];
   const int64_t a_step = 8 * (int64_t)KR, b_step = a_step * a.ldb;
   const char* a_next = (const char*)(a.A + m0 * a.lda) + s_begin * a_step;

@@ -1,18 +1,23 @@
 // Batched products and multi-modular (CRT) products.
 //
-// mm_modp_batched: every product is planned on its own; products that share
-// a kernel configuration run together, up to kMaxBatch per launch, with the
-// job table in the kernel arguments.  INT8-form products first get their
-// digit planes (one workspace for the whole batch), then one digit GEMM per
-// digit count.  The batch is enqueued on one stream with no host
-// synchronisation, so with a caller workspace it can be captured into a HIP
-// graph and replayed.
+// mm_modp_batched: every product is planned on its own; those of an AUTO batch may
+// then move to INT8 words for launches that they share (move_to_int8), and on INT8
+// words to the residue form.  FP64-word products of one configuration run together,
+// up to kMaxBatch per launch, with the job table in the kernel arguments.  INT8
+// products have one workspace for the whole batch: those in the residue form share a
+// conversion, a product launch per tile size and their recombinations, the others
+// one launch of digit planes and one of the digit GEMM for every 64 of them
+// (batch_launch = 1: planes per product, one GEMM per digit count).  The batch is
+// enqueued on one stream with no host synchronisation, so with a caller workspace it
+// can be captured into a HIP graph and replayed.
 //
-// mm_modp_crt: one integer pair A, B against many moduli.  When k fits one
-// exact int32 block the integers are digitised once, one digit GEMM forms
-// the digit-weight sums of A B, and each modulus reduces those sums in the
-// epilogue; otherwise A and B are reduced mod each p on the device and the
-// products run as a batch.
+// mm_modp_crt: one integer pair A, B against many moduli.  AUTO jobs run in the
+// residue form where it is estimated faster, and for any k beyond one exact int32
+// block.  Else, within one block, the integers are digitised once, one digit GEMM
+// forms the digit-weight sums of A B, and each modulus reduces those sums in the
+// epilogue; beyond it (opts->form set, or a workspace too small for the residue
+// planes) A and B are reduced mod each p on the device and the products run one by
+// one.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -403,7 +408,7 @@ int mm_modp_crt(const mmp_opts* opts, const uint64_t* A, int64_t lda, const uint
         st = hip_status(launch_crt(d, c, stream));
       }
     } else {
-      // reduce mod each p on the device, then the products as one batch
+      // reduce mod each p on the device, then the products one by one
       const size_t per = align_up(8 * (size_t)(m * k + k * n)) + align_up(int8_workspace_bytes(kMaxDigits, m, n, k));
       std::vector<mmp_job> jobs(nprimes);
       for (int i = 0; i < nprimes && st == MMP_OK; i++) {

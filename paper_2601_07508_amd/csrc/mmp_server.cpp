@@ -112,8 +112,10 @@ struct mmp_server {
   }
 
   // The request's footprint: operands, result and word copies; for the
-  // INT8 form exactly the digit planes the launch allocates (resident planes
-  // are not counted again), and the k-range residues of a lone launch.
+  // INT8 form exactly the digit planes the launch needs (resident planes
+  // are not counted again), and the k-range residues of a lone launch.  The
+  // workspace that a launch takes may be up to a quarter larger, or a kept block of
+  // up to four times its size: within the 2 GiB a device that are kept between calls.
   size_t request_footprint(const Request& r) const {
     const mmp_job& j = r.job;
     size_t fp;
