@@ -62,7 +62,7 @@ typedef enum {
 /* Word forms. */
 enum {
   MMP_FORM_AUTO = 0,        /* planner picks the faster form for (p, shape); a
-                               single product planned on INT8 words then runs
+                               product planned on INT8 words then runs
                                on its signed digits, or, where that is the
                                faster way to the same result, on its residues
                                modulo pairwise coprime moduli of one INT8 word
@@ -96,19 +96,29 @@ typedef struct {
                              and is integral before computing (MMP_ERANGE);
                              the call then waits for the check to finish */
   int tile;               /* 0: planner's tile; else a tile id from mmp_plan_t */
-  int strict_fmod;        /* 1: every in-loop reduction is the full Alg. 1;
-                             0: the planner may use the correction-free form
-                             where its range check allows (see mmp_plan_t) */
+  int strict_fmod;        /* 1: every in-loop reduction is the full Alg. 1, and
+                             an AUTO product that mmp_plan gives to FP64 words
+                             stays on them; 0: the planner may use the
+                             correction-free form where its range check allows
+                             (see mmp_plan_t) */
   int64_t force_kblock;   /* 0: planner's k-block; else the number of k-terms
                              accumulated between reductions (<= the bound;
                              FP64 form: at most 16, or a multiple of 4 up to
                              2^26; INT8 form: a multiple of 64 up to
                              kblock_int8) */
   void *workspace;        /* optional caller-owned device workspace; when
-                             NULL the library allocates stream-ordered memory
-                             from the device's default pool.  Pass one (of at
+                             NULL the library takes one that it keeps between
+                             calls (up to 256 MB each and 2 GiB per device; see
+                             mmp_release_workspaces) or allocates stream-ordered
+                             memory from the device's default pool, as a call
+                             under capture always does.  Pass one (of at
                              least the queried size) to capture a call into a
-                             HIP graph. */
+                             HIP graph without an allocation.  A single AUTO
+                             product takes its fastest form only where the
+                             workspace holds what that needs: up to 20 bytes per
+                             entry of A and of B (k rounded up to 64) and, for
+                             each of its k-ranges, of C (in whole 256 x 256
+                             tiles). */
   size_t workspace_bytes; /* size of workspace */
   int extended_block;     /* FP64 form, 1: accumulate over the whole signed
                              exact range [-2^t, 2^t] instead of [0, 2^t]: each
@@ -135,12 +145,16 @@ typedef struct {
                              word bounds).  Exclusive with extended_block and
                              strict_fmod.  0: the paper's words. */
   int batch_launch;       /* mm_modp_batched, INT8-form products:
-                             0 = one launch of the digit planes and one of
-                             the digit GEMM for every 64 products, whatever
-                             their digit counts, when the batch has two or
-                             more; 1 = per digit count (planes per product,
-                             then one GEMM per digit count and 16
-                             products); 2 = the one-launch form always.
+                             0 = of an AUTO batch, those that are faster so
+                             in the residue form, with one conversion, one
+                             product launch per tile size and one
+                             recombination per 16 products, for every 64 of
+                             them; the others with one launch of the digit
+                             planes and one of the digit GEMM for every 64,
+                             whatever their digit counts, when the batch has
+                             two or more; 1 = digits, per digit count (planes
+                             per product, then one GEMM per digit count and 16
+                             products); 2 = digits, the one-launch form always.
                              Other entry points: must be zero. */
   const mmp_operand_t *prepared_a; /* mm_modp_async only: A's digit planes
                              from mmp_prepare_operand (same p and shape);
@@ -173,13 +187,16 @@ typedef struct {
   int digits_a, digits_b; /* INT8 form: signed base-256 digits per operand */
   int64_t kblock_int8;    /* INT8 form: k-terms per int32 accumulation block */
   double q;               /* fl(1/p) */
-  double est_seconds;     /* planner's cost-model estimate (0 if unknown) */
+  double est_seconds;     /* planner's cost-model estimate (0 if unknown): of
+                             `form` as named here, on INT8 words the faster of
+                             digits and residues.  A call may run an AUTO product
+                             in another form (mm_modp_async, mm_modp_batched) */
   int splits;             /* split-K k-ranges (1: none) */
   size_t workspace_bytes; /* device workspace the call needs (an AUTO call
                              on INT8 words: what its digits need; given a
                              caller's workspace too small for the residues'
-                             planes, up to 20 bytes per entry of A, B and C,
-                             it runs on the digits) */
+                             planes (see mmp_opts.workspace), it runs on the
+                             digits) */
   int centered;           /* 1: centered words and the round-to-nearest
                              in-loop reduction (mmp_opts.centered_words) */
   int biased;             /* 1: the correction-free in-loop reduction is the
@@ -224,8 +241,8 @@ int mm_modp(uint64_t p, int u, int v, int64_t m, int64_t n, int64_t k,
    return MMP_EINVAL; the server plans such a request in the INT8 form.
    An AUTO call that mmp_plan gives to FP64 words runs on INT8 words where
    those are estimated faster from measured times and their memory is there
-   (a caller's workspace that holds it, or the library's own outside a
-   capture); the result is the same. */
+   (a caller's workspace that holds it, or up to 16 GiB of the library's own
+   outside a capture); the result is the same. */
 int mm_modp_async(const mmp_opts *opts, uint64_t p, int u, int v, int64_t m,
                   int64_t n, int64_t k, const double *A, int64_t lda,
                   const double *B, int64_t ldb, double *C, int64_t ldc,
@@ -272,12 +289,17 @@ int mmp_prepare_operand(uint64_t p, int side, const double *M, int64_t rows,
 /* ---------------------------------------------------------------- batches */
 
 /* count independent products C_i = A_i B_i mod p_i (each job with its own
- * shape, modulus and words), enqueued on one stream.  Products that share a
- * kernel configuration run in one launch (up to 16 per launch); no host
- * synchronisation happens unless validate_entries is set, so with a caller
- * workspace of mmp_workspace_batched() bytes the call can be captured into a
- * HIP graph.  The batched block products follow the paper's closing
- * perspective (Section 6).  Outputs must not overlap each other. */
+ * shape, modulus and words), enqueued on one stream.  FP64-word products that
+ * share a kernel configuration run in one launch (up to 16 per launch), INT8
+ * products as mmp_opts.batch_launch says.  AUTO products of a batch that
+ * mmp_plan gives to FP64 words run on INT8 words where that is estimated faster
+ * for the batch, with up to 8 GiB of planes that no product's own plan calls
+ * for (residue planes included); with a caller's workspace smaller than
+ * mmp_workspace_batched(), or under capture without one, every product runs as
+ * mmp_plan says.  No host synchronisation happens unless validate_entries is
+ * set, so with a caller workspace of mmp_workspace_batched() bytes the call can
+ * be captured into a HIP graph.  The batched block products follow the paper's
+ * closing perspective (Section 6).  Outputs must not overlap each other. */
 int mm_modp_batched(const mmp_job *jobs, int count, const mmp_opts *opts,
                     void *stream);
 
@@ -297,9 +319,10 @@ size_t mmp_workspace_batched(const mmp_job *jobs, int count,
  * cores and every modulus reduces them (one GEMM launch for up to 64
  * moduli); or, where that is faster and for any longer k, the integer product
  * is formed modulo one-byte moduli (one INT8 product each) and every prime
- * reduces the integer recombined from them.  Otherwise (a workspace too small
- * for that, or opts->form set) A and B are reduced mod each p on the device
- * and the products run one by one.  validate_entries checks the entry bound
+ * reduces the integer recombined from them.  Without that (a workspace too small
+ * for it, or opts->form set), within one int32 block the digit-weight sums serve,
+ * and beyond it A and B are reduced mod each p on the device and the products run
+ * one by one.  validate_entries checks the entry bound
  * (MMP_ERANGE).  Capturable into a graph with a caller workspace of
  * mmp_workspace_crt() bytes. */
 int mm_modp_crt(const mmp_opts *opts, const uint64_t *A, int64_t lda,
@@ -323,8 +346,11 @@ size_t mmp_workspace_crt(int64_t m, int64_t n, int64_t k, int entry_bits,
  *      modulus, Prop. Joris);
  *   out: DEVICE, X as `limbs` little-endian 64-bit words in planes: word w of
  *      entry (i, j) at out[(w m + i) ldo + j]; limbs must hold M - 1.
- * Computed on the device: Garner's mixed-radix digits in binary64 modular
- * arithmetic (Alg. 1, Alg. 2), then Horner into the limbs.  Asynchronous on
+ * Computed on the device: from 5 to 48 moduli (while their constants fit) as a
+ * contraction, X = sum_t g_t (M / p_t) - h M with g_t by Alg. 2 and the bytes of
+ * the g_t against those of the constants on the INT8 matrix cores; else Garner's
+ * mixed-radix digits in binary64 modular arithmetic (Alg. 1, Alg. 2), then
+ * Horner into the limbs.  The same integers either way.  Asynchronous on
  * `stream`; MMP_EINVAL for bad arguments, before any launch. */
 int mmp_crt_reconstruct(const double *const *C, int64_t ldc,
                         const uint64_t *moduli, int nmoduli, int64_t m,
@@ -338,7 +364,9 @@ int mmp_crt_reconstruct(const double *const *C, int64_t ldc,
  * scheduler thread admits queued requests in arrival order while a request
  * slot is free and the device footprint in flight (mmp_footprint of each
  * admitted request: operands, result and word or digit copies, per the
- * storage cost of Section 3.3) stays within hbm_budget; all requests
+ * storage cost of Section 3.3) stays within hbm_budget (the workspaces that the
+ * library keeps between calls, up to 2 GiB a device, lie outside it as far as
+ * they are rounded up or idle); all requests
  * admitted in one scheduling step are launched together (products sharing a
  * kernel configuration in one launch) on the least busy of 4 streams, so
  * requests that arrive while others run start beside them and their work
