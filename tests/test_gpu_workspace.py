@@ -1,5 +1,6 @@
 """Workspaces kept between calls: results stay exact when calls of different
-sizes share them over several streams and threads, and beside a graph capture."""
+sizes share them over several streams and threads (beside a graph capture:
+test_gpu_capture.py), and they stay within their bounds."""
 import ctypes
 import sys
 import threading
