@@ -34,6 +34,7 @@ int mmp_autotune(uint64_t p, int64_t m, int64_t n, int64_t k, const mmp_opts* op
     const bool extended = base.extended_block != 0;
     const bool centered = base.centered_words != 0;
     if (base.form != MMP_FORM_AUTO || base.force_kblock || base.tile) return MMP_EINVAL;
+    if (base.batch_launch) return MMP_EINVAL;  // a batch option
     mmp_plan_t probe;
     if (int st = plan(p, 0, 0, m, n, k, &base, &probe)) return st;  // validates p and sizes
 

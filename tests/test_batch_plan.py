@@ -71,3 +71,13 @@ def test_options_of_fp64_words_keep_them(option):
     dims = [(512, 512, 512, P36)] * 4
     assert mmp.plan(P36, 512, 512, 512, splits=1, **{option: True})["form"] == mmp.FORM_FP64_WORDS
     assert workspace(dims) > 0 and workspace(dims, **{option: True}) == 0
+
+
+@pytest.mark.parametrize("launch", [1, 2])
+def test_batch_option_is_refused_elsewhere(launch):
+    # before any device work
+    lib, o, best, tried = mmp.lib(), mmp._opts(batch_launch=launch), mmp.MmpPlan(), ctypes.c_int(-1)
+    assert lib.mmp_autotune(P36, 64, 64, 64, ctypes.byref(o), ctypes.byref(best), ctypes.byref(tried)) == -1
+    fake = [ctypes.c_void_p(0x10000000 * (i + 1)) for i in range(3)]
+    args = (ctypes.byref(o), P36, 0, 0, 8, 8, 8, fake[0], 8, fake[1], 8, fake[2], 8, None)
+    assert lib.mm_modp_async(*args) == -1 and lib.mm_modp_static(*args) == -1
