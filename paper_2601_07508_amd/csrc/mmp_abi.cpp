@@ -174,6 +174,7 @@ static size_t block_size(size_t bytes) {
 // Gives every kept block of the device that no call holds back to its memory pool,
 // after the work that used it, and what the pool has free to the device.
 static int give_back(int dev) {
+  Relaxed relaxed;
   hipStream_t s;
   if (int e = (int)hipStreamCreateWithFlags(&s, hipStreamNonBlocking)) return e;
   int e = 0;

@@ -139,6 +139,7 @@ def test_another_threads_calls_during_a_capture():
         try:
             for i, D in enumerate(outs):
                 mmp.mm_modp_async(X, Y, D, q, stream=streams[i % 2], form=mmp.FORM_INT8_WORDS)
+            mmp.release_workspaces()
         except Exception as e:  # reported below, in the test's own thread
             errors.append(e)
 
